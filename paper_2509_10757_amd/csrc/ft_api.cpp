@@ -312,7 +312,7 @@ ft_status check_pyramid_build(ft_context *ctx, const ft_image *img, const ft_sca
     int64_t bytes = 0;
     if (!pyramid_layout(img->width, img->height, sc, &want, &bytes))
         return fail(ctx, FT_ERR_INVALID_ARGUMENT, "%s: a pyramid level of the image would be empty", what);
-    for (int l = 1; l < kLevels; ++l)   // levels shrink (the build stages at most kPyrRows + 1 rows per tile)
+    for (int l = 1; l < kLevels; ++l)   // levels shrink
         if (want.width[l] > img->width || want.height[l] > img->height)
             return fail(ctx, FT_ERR_INVALID_ARGUMENT, "%s: pyramid level %d is larger than the image", what, l);
     for (int l = 0; l < kLevels; ++l)
@@ -321,7 +321,8 @@ ft_status check_pyramid_build(ft_context *ctx, const ft_image *img, const ft_sca
     return FT_OK;
 }
 
-void bind_pyramid_build(DevJob &J, const ft_image *L, const ft_image *R, const ft_pyramid *pl, const ft_pyramid *pr)
+void bind_pyramid_build(DevJob &J, const ft_image *L, const ft_image *R, const ft_pyramid *pl, const ft_pyramid *pr,
+                        int images)
 {
     J.imgL = L->data;
     J.imgR = R ? R->data : nullptr;
@@ -335,6 +336,10 @@ void bind_pyramid_build(DevJob &J, const ft_image *L, const ft_image *R, const f
         J.lv_w[l] = pl->width[l];
         J.lv_h[l] = pl->height[l];
     }
+    // Rows of a wave's strip, by the images built in one launch: short strips
+    // fill the chip with one image (1281x719: 7.2 us at 4 rows, 10.9 at 16), long
+    // ones spread a strip's set-up over more rows (32 images of 752x480 and more)
+    pyr_plan(J, images <= 2 ? 2 : images <= 16 ? 3 : 4);
 }
 
 ft_status build_pinhole(ft_context *ctx, DevJob &J, const ft_keypoints *L, const ft_keypoints *R,
@@ -659,6 +664,8 @@ ft_status build_batch(ft_context *ctx, Lane &lane, const ft_frame_job *jobs, int
     ft_status st;
     DevJob *table = reinterpret_cast<DevJob *>(lane.h_table + ctx->layout.jobs_off);
     int64_t kp_total = 0, map_total = 0;
+    int images = 0;   // images whose pyramids the batch builds
+    for (int f = 0; f < n; ++f) images += jobs[f].kind == FT_JOB_PINHOLE && jobs[f].build_pyramids ? 2 : 0;
     for (int f = 0; f < n; ++f) {
         const ft_frame_job &jb = jobs[f];
         const bool stereo = jb.kind == FT_JOB_PINHOLE || jb.kind == FT_JOB_FISHEYE;
@@ -678,7 +685,7 @@ ft_status build_batch(ft_context *ctx, Lane &lane, const ft_frame_job *jobs, int
                 if (jb.image_left.width != jb.image_right.width || jb.image_left.height != jb.image_right.height ||
                     jb.image_left.pitch != jb.image_right.pitch)
                     return fail(ctx, FT_ERR_INVALID_ARGUMENT, "batch: job %d stereo images differ in size or pitch", f);
-                bind_pyramid_build(J, &jb.image_left, &jb.image_right, &jb.pyr_left, &jb.pyr_right);
+                bind_pyramid_build(J, &jb.image_left, &jb.image_right, &jb.pyr_left, &jb.pyr_right, images);
             }
         } else if (jb.kind == FT_JOB_FISHEYE) {
             if ((st = build_fisheye(ctx, J, &jb.left, &jb.right, &jb.scales, &jb.fisheye,
@@ -1315,7 +1322,7 @@ ft_status ft_build_pyramid(ft_context *ctx, void *stream, const ft_image *image,
         return st;
     DevJob J{};
     fill_scales(J, scales);
-    bind_pyramid_build(J, image, nullptr, pyr, nullptr);
+    bind_pyramid_build(J, image, nullptr, pyr, nullptr, 1);
     return launch_one(ctx, J, (hipStream_t)stream, true, false);
 }
 

@@ -23,8 +23,7 @@ constexpr int kRefinePerWG = 4;       // pinhole refinement: one wave per match
 constexpr int kRefineLds = 1024;      // bytes of LDS per refining wave (patch + strip)
 constexpr int kRefineQPerWG = 16;     // ... 11x11 window, +-5 shifts: four matches per wave
 constexpr int kRefineQLds = 800;      // bytes of LDS per match (11 x 12 + 11 x 24 16-bit values)
-constexpr int kPyrRows = 16;          // image pyramid: level-0 rows per workgroup
-constexpr int kMaxPyrW = 1536;        // widest level-0 image the pyramid build stages in LDS
+constexpr int kMaxPyrW = 1536;        // widest level-0 image of the pyramid build (and of the ORB detector's LDS rows)
 constexpr int kRotBinsMax = 64;       // rotation histogram bins of the last-frame search
 
 enum Phase : int {
@@ -151,6 +150,8 @@ struct DevJob {
     const FT_G uint8_t *imgL, *imgR;  // level-0 images, row pitch img_pitch (null: no build)
     FT_G uint8_t *pyr_outL, *pyr_outR;
     int32_t img_w, img_h, img_pitch;
+    int32_t pyr_rows_log2;            // rows of one wave's strip (at most 64)
+    int32_t pyr_first[kLevels + 1];   // strips before each level (pyr_plan)
     // last-frame search by projection (view 0; pos / mdesc / nM hold the points)
     const FT_G uint8_t *l_oct;        // octave of the last-frame keypoint of each point
     const FT_G float *l_ang, *k_ang;  // orientations (degrees): last-frame keypoints, current keypoints
@@ -182,6 +183,9 @@ struct BatchArgs {
     const DevJob *p;
     TileMap map;
 };
+
+// Strips of the pyramid build (ft_kernels.hip), once the levels' sizes are set.
+void pyr_plan(DevJob &J, int rows_log2);
 
 // Per-job tile counts of each phase for the given shapes.
 void job_tiles(const DevJob &J, const Shapes &s, bool do_stereo, bool do_search,

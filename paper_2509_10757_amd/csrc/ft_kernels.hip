@@ -48,6 +48,10 @@ struct Desc {
 // vector type: arrays of it stay in registers, unlike arrays of uint4).
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
+// A dword at any byte address; four dwords from a dword boundary.
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef v4u v4u_dw __attribute__((aligned(4)));
+
 // Keypoints per thread whose loads are issued together in the setup sorts and
 // the median pass (a strided loop body unrolled; surplus entries masked).
 constexpr int kSortUnroll = 4;
@@ -206,176 +210,292 @@ __device__ __forceinline__ int cell_coord(float v, float lo, float inv, int n)
 // level-0 axis n_in long: source pixel floor(s) and weight floor(256 * frac(s)),
 // clamped to the first and last pixel.  Returns pixel | weight << 16.
 //
-// floor(num / den) by a reciprocal estimate and one correction step each way
-// (num < 2^28 and den < 2^15, so the estimate is off by at most one).
-__device__ __forceinline__ int div_floor_small(int num, int den, int &rem)
-{
-    int q = (int)floorf((float)num * __builtin_amdgcn_rcpf((float)den));
-    int r = num - q * den;
-    if (r < 0) {
-        --q;
-        r += den;
-    } else if (r >= den) {
-        ++q;
-        r -= den;
-    }
-    rem = r;
-    return q;
-}
-
+// Both come from one quotient, t = floor(256 num / den): pixel t >> 8, weight
+// t & 255.  num < 2^26, den <= 2^13 and t <= 2^20, so the reciprocal estimate is
+// off by at most one, and the remainder, at most a few den in size, is exact
+// modulo 2^32.
 __device__ __forceinline__ uint32_t pyr_tap(int x, int n_in, int n_out)
 {
     const int num = (2 * x + 1) * n_in - n_out;
     if (num <= 0) return 0u;
-    const int den = 2 * n_out;
-    int r;
-    int q = div_floor_small(num, den, r);
-    int r2;
-    int wq = div_floor_small(256 * r, den, r2);
-    if (q >= n_in - 1) {
-        q = n_in - 1;
-        wq = 0;
+    const uint32_t den = 2u * (uint32_t)n_out;
+    uint32_t t = (uint32_t)floorf((float)num * 256.0f * __builtin_amdgcn_rcpf((float)den));
+    const int r = (int)(((uint32_t)num << 8) - t * den);
+    t = r < 0 ? t - 1u : r >= (int)den ? t + 1u : t;
+    const uint32_t q = t >> 8;
+    return q >= (uint32_t)(n_in - 1) ? (uint32_t)(n_in - 1) : q | ((t & 255u) << 16);
+}
+
+// A wave's strip: 64 lanes of 4 output columns (level 0: 1024 bytes of a row,
+// which may start up to 3 bytes past a dword boundary) by 2^pyr_rows_log2 rows.
+// Sets the strips of each level as prefix sums.
+constexpr int kPyrCols = 4, kPyrStripW = 64 * kPyrCols, kPyrCopyW = 1024;
+void pyr_plan(DevJob &J, int rows_log2)
+{
+    J.pyr_rows_log2 = rows_log2;
+    J.pyr_first[0] = 0;
+    for (int l = 0; l < kLevels; ++l) {
+        const int nx = l == 0 ? div_up(J.lv_w[0] + 3, kPyrCopyW) : div_up(J.lv_w[l], kPyrStripW);
+        J.pyr_first[l + 1] = J.pyr_first[l] + nx * div_up(J.lv_h[l], 1 << rows_log2);
     }
-    return (uint32_t)q | ((uint32_t)wq << 16);
 }
 
-// LDS of one pyramid tile: kPyrRows + 1 staged level-0 rows, then per level
-// the first output row, the row count and the row taps of the tile's rows.
-constexpr int kPyrStage = (kPyrRows + 1) * kMaxPyrW;
-constexpr int kPyrRowTaps = kPyrRows + 2;                   // output rows of one level in a tile (bound)
-constexpr int kPyrMeta = kPyrStage;                         // int [kLevels][2]: first row, count
-constexpr int kPyrRowTab = kPyrMeta + 2 * kLevels * 4;      // uint32 [kLevels][kPyrRowTaps]
-constexpr int kPyrLds = kPyrRowTab + kLevels * kPyrRowTaps * 4;
-static_assert((kLevels - 1) * kPyrRowTaps <= kWG, "one thread per row tap of levels 1..7");
+// How a lane reads the taps of four neighbouring columns of a level that is
+// 1 / s of the image.  From a dword boundary at or below the first tap, 16 bytes
+// hold all four pixel pairs while s <= 11/3; realigned to the first tap, column
+// k's pair starts floor(k s) or one more bytes in, so it lies in a fixed pair of
+// dwords: the first two for every column while s <= 2 (kNear), later ones for
+// columns 2 and 3 beyond (kMid, kFar).  kAny, for any other level or an image
+// under 16 columns, reads the pixels one by one.
+enum PyrReach { kNear, kMid, kFar, kAny };
 
-// First output row y of a level h rows tall whose top tap row is at least Y
-// (0 <= Y < H): the tap is floor(((2y + 1) H - h) / (2h)), and its clamp to
-// H - 1 never takes it below Y, so y is the smallest with
-// (2y + 1) H - h >= 2hY: ceil((2hY + h - H) / (2H)), and at least 0.
-__device__ __forceinline__ int pyr_first_row(int Y, int H, int h)
+// Columns x .. x + 3 of output rows [ylo, yhi) of one level; `row_taps`: lane r
+// holds the row tap of output row ylo + r.  A lane reads one aligned dwordx4
+// per source row, realigns it (v_alignbyte), and blends a pixel pair per column
+// with a byte permute and a 16-bit dot product; the two blended rows of an
+// output row are combined by 24-bit multiply-adds.  All arithmetic is exact, so
+// the order of the blends does not matter.  Up to s = 2 neighbouring output rows
+// share source rows, so those are walked one after another and blended once;
+// beyond, each output row takes its two.  (Misaligned vector loads take one
+// lane per cycle here: a wave's dwordx2 33 cycles, its dwordx4 65, against 17
+// aligned.)  Every dword read holds at least one byte of the image.
+template <PyrReach kReach>
+__device__ __forceinline__ void pyr_resample(const FT_G uint8_t *src, int W, int H, int pitch, FT_G uint8_t *dst, int wl,
+                                             int x, int ylo, int yhi, uint32_t row_taps, bool full)
 {
-    const int num = 2 * h * Y + h - H;
-    if (num <= 0) return 0;
-    return (num + 2 * H - 1) / (2 * H);
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    constexpr bool kShared = kReach == kNear;
+    uint32_t wgt[kPyrCols], sel[kPyrCols];
+    int x0[kPyrCols];
+    _Pragma("unroll") for (int k = 0; k < kPyrCols; ++k)
+    {
+        const uint32_t c = pyr_tap(min(x + k, wl - 1), W, wl);
+        x0[k] = (int)(c & 0xFFFFu);
+        const uint32_t a = c >> 16;
+        wgt[k] = (256u - a) | (a << 16);
+        const int first = kReach == kFar && k == 3 ? 8 : kReach >= kMid && k >= 2 ? 4 : 0;
+        // bytes o and o + 1 of the dword pair as a 16-bit pair (0x0C: zero)
+        sel[k] = 0x0C010C00u + 0x00010001u * (uint32_t)(x0[k] - x0[0] - first);
+    }
+    struct Row {
+        uint32_t d[4];
+    };
+    auto load = [&](const FT_G uint8_t *row) {
+        Row v;
+        if constexpr (kReach == kAny) {   // (a pixel pair per column, in place)
+            _Pragma("unroll") for (int k = 0; k < kPyrCols; ++k)
+                v.d[k] = (uint32_t)row[x0[k]] | ((uint32_t)row[min(x0[k] + 1, W - 1)] << 16);
+        } else {
+            // (past the row's end lie the next row's bytes, whose weights are 0)
+            const uint32_t sh = (uint32_t)reinterpret_cast<uintptr_t>(row) & 3u;
+            const uint32_t off = ((uint32_t)x0[0] + sh) & ~3u;
+            const v4u q = *reinterpret_cast<const FT_G v4u_dw *>(row - sh + off);
+            _Pragma("unroll") for (int i = 0; i < 4; ++i) v.d[i] = q[i];
+        }
+        return v;
+    };
+    auto blend = [&](const Row &v, uint32_t sh, uint32_t h[kPyrCols]) {
+        uint32_t e[4] = {v.d[0], v.d[1], v.d[2], v.d[3]};
+        if constexpr (kReach != kAny) {
+            const uint32_t a = (uint32_t)x0[0] + sh;   // (v_alignbyte takes it modulo 4)
+            _Pragma("unroll") for (int i = 0; i < 3; ++i) e[i] = __builtin_amdgcn_alignbyte(v.d[i + 1], v.d[i], a);
+            e[3] = __builtin_amdgcn_alignbyte(0u, v.d[3], a);
+        }
+        _Pragma("unroll") for (int k = 0; k < kPyrCols; ++k)
+        {
+            const int j = kReach == kFar && k == 3 ? 2 : kReach >= kMid && k >= 2 ? 1 : 0;
+            const uint32_t pr = kReach == kAny ? e[k] : __builtin_amdgcn_perm(e[j + 1], e[j], sel[k]);
+            h[k] = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, pr), __builtin_bit_cast(u16x2, wgt[k]), 0u, false);
+        }
+    };
+    FT_G uint8_t *d = dst + (size_t)ylo * wl + x;
+    auto write = [&](const uint32_t top[kPyrCols], const uint32_t bot[kPyrCols], uint32_t b) {
+        uint32_t o[kPyrCols];
+        _Pragma("unroll") for (int k = 0; k < kPyrCols; ++k)
+            o[k] = __umul24(bot[k], b) + (__umul24(top[k], 256u - b) + 32768u);
+        // bits 16..23 of the four sums
+        const uint32_t px = __builtin_amdgcn_perm(__builtin_amdgcn_perm(o[3], o[2], 0x0C0C0602u),
+                                                  __builtin_amdgcn_perm(o[1], o[0], 0x0C0C0602u), 0x05040100u);
+        if (full) {
+            *reinterpret_cast<FT_G u32_any *>(d) = px;
+        } else if (wl - x >= kPyrCols) {
+            *reinterpret_cast<FT_G u32_any *>(d) = px;
+        } else {
+            _Pragma("unroll") for (int k = 0; k < kPyrCols - 1; ++k) if (k < wl - x) d[k] = (uint8_t)(px >> (8 * k));
+        }
+        d += wl;
+    };
+    auto tap_of = [&](int r) { return (uint32_t)__builtin_amdgcn_readlane((int)row_taps, r); };
+    auto mod4 = [](const FT_G uint8_t *q) { return (uint32_t)reinterpret_cast<uintptr_t>(q) & 3u; };
+    const int n_rows = yhi - ylo;
+    uint32_t t = tap_of(0);
+    if constexpr (kShared) {
+        // every source row from the first tap to the one below the last; a row
+        // whose predecessor is the next output row's tap completes that row
+        constexpr int kChunk = 4;   // source rows whose loads are issued together
+        const int y0 = (int)(t & 0xFFFFu), y1 = min((int)(tap_of(n_rows - 1) & 0xFFFFu) + 1, H - 1);
+        uint32_t top[kPyrCols] = {};
+        int r = 0;
+        const FT_G uint8_t *row = src + (size_t)y0 * pitch;
+        for (int y = y0; y <= y1; y += kChunk) {
+            Row v[kChunk];
+            const FT_G uint8_t *q = row;
+            _Pragma("unroll") for (int u = 0; u < kChunk; ++u)
+            {
+                v[u] = load(q);
+                if (y + u < y1) q += pitch;
+            }
+            _Pragma("unroll") for (int u = 0; u < kChunk; ++u)
+            {
+                if (y + u > y1) break;
+                uint32_t bot[kPyrCols];
+                blend(v[u], mod4(row), bot);
+                row += pitch;
+                if (y + u == (int)(t & 0xFFFFu) + 1) {
+                    write(top, bot, t >> 16);
+                    t = tap_of(min(++r, n_rows - 1));
+                }
+                _Pragma("unroll") for (int k = 0; k < kPyrCols; ++k) top[k] = bot[k];
+            }
+        }
+        // the last output row's tap is the image's last row (its other weight is 0)
+        if (r < n_rows) write(top, top, 0u);
+    } else {
+        // two source rows per output row
+        constexpr int kChunk = 2;   // output rows whose loads are issued together
+        for (int r0 = 0; r0 < n_rows; r0 += kChunk) {
+            Row v[kChunk], w[kChunk];
+            uint32_t sv[kChunk], sw[kChunk], b[kChunk];
+            _Pragma("unroll") for (int u = 0; u < kChunk; ++u)
+            {
+                t = tap_of(min(r0 + u, n_rows - 1));
+                const int ys = (int)(t & 0xFFFFu);
+                const FT_G uint8_t *p0 = src + (size_t)ys * pitch, *p1 = ys < H - 1 ? p0 + pitch : p0;
+                v[u] = load(p0);
+                w[u] = load(p1);
+                sv[u] = mod4(p0);
+                sw[u] = mod4(p1);
+                b[u] = t >> 16;
+            }
+            _Pragma("unroll") for (int u = 0; u < kChunk; ++u)
+            {
+                if (r0 + u >= n_rows) break;
+                uint32_t top[kPyrCols], bot[kPyrCols];
+                blend(v[u], sv[u], top);
+                blend(w[u], sw[u], bot);
+                write(top, bot, b[u]);
+            }
+        }
+    }
 }
 
-// One tile: image `side` (0 left, 1 right) of the frame, level-0 rows
-// [Y0, Y0 + kPyrRows).  Stages those rows and the next in LDS, copies them to
-// level 0 and writes every output row of levels 1..7 whose top tap row is
-// among them: each source row is read from memory once and each output byte
-// written once.  A thread owns output columns (of all levels in turn), takes
-// the column's tap once and walks the tile's rows of that level; neighbouring
-// threads write neighbouring bytes of a row.
-__device__ __forceinline__ void ph_pyramid(const DevJob &J, int tile, unsigned char *smem)
+// Rows [ylo, yhi) of level 0: a lane takes dwords lane, lane + 64, .. of the
+// 1024-byte strip bx of each destination row, counted from the row's dword
+// boundary (neighbouring lanes on neighbouring dwords), realigned from the
+// source's dwords, every one of which holds at least one byte of the row; the
+// dwords at a row's two ends are written byte by byte.
+__device__ __forceinline__ void pyr_copy(const FT_G uint8_t *src, int W, int pitch, FT_G uint8_t *dst, int bx, int ylo, int yhi)
 {
-    const int W = J.img_w, H = J.img_h, pitch = J.img_pitch;
-    const int per = div_up(H, kPyrRows);
-    const int side = tile / per;
+    const int lane = threadIdx.x & 63;
+    constexpr int kRows = 4, kDw = 4;   // rows and dwords per lane whose loads are issued together
+    for (int y0 = ylo; y0 < yhi; y0 += kRows) {
+        uint32_t lo[kRows][kDw], hi[kRows][kDw] = {};
+        _Pragma("unroll") for (int r = 0; r < kRows; ++r)
+        {
+            const int y = min(y0 + r, yhi - 1);
+            const FT_G uint8_t *s = src + (size_t)y * pitch;
+            const int da = (int)(reinterpret_cast<uintptr_t>(dst + (size_t)y * W) & 3u);
+            const int sa = (int)(reinterpret_cast<uintptr_t>(s) & 3u);
+            const int sh = (sa - da) & 3;
+            const FT_G uint32_t *dw = reinterpret_cast<const FT_G uint32_t *>(s - sa);
+            const int last = (sa + W - 1) >> 2;
+            const int d0 = (sa - da - sh) >> 2;   // source dword of the row's destination dword 0 (-1 or 0)
+            _Pragma("unroll") for (int i = 0; i < kDw; ++i)
+            {
+                const int q = d0 + kPyrCopyW / 4 * bx + 64 * i + lane;
+                lo[r][i] = dw[min(max(q, 0), last)];
+                if (sh) hi[r][i] = dw[min(max(q + 1, 0), last)];
+            }
+        }
+        _Pragma("unroll") for (int r = 0; r < kRows; ++r)
+        {
+            if (y0 + r >= yhi) break;
+            FT_G uint8_t *row = dst + (size_t)(y0 + r) * W;
+            const int da = (int)(reinterpret_cast<uintptr_t>(row) & 3u);
+            const uint32_t sh = (uint32_t)(reinterpret_cast<uintptr_t>(src + (size_t)(y0 + r) * pitch) - (uintptr_t)da) & 3u;
+            _Pragma("unroll") for (int i = 0; i < kDw; ++i)
+            {
+                const int p = 4 * (kPyrCopyW / 4 * bx + 64 * i + lane) - da;   // row offset of the dword
+                const uint32_t e = __builtin_amdgcn_alignbyte(hi[r][i], lo[r][i], sh);
+                if (p >= 0 && p + 4 <= W) {
+                    *reinterpret_cast<FT_G uint32_t *>(row + p) = e;
+                } else if (p < W) {
+                    _Pragma("unroll") for (int k = 0; k < 4; ++k)
+                        if (p + k >= 0 && p + k < W) row[p + k] = (uint8_t)(e >> (8 * k));
+                }
+            }
+        }
+    }
+}
+
+// One wave's strip of image `side` (0 left, 1 right) of the frame.  The strips
+// read level 0 straight from memory (it stays in L2; up to seven levels read
+// it), so there is no staging, no barrier and no shared tile: what bounds the
+// build is vector issue and the strips' chains of loads, and a single image
+// needs many short waves rather than few workgroups.  (1281x719, one image: 42.5
+// us as 16-row workgroups with the rows staged in LDS, 7.2 us as strips; 16
+// images of 752x480 in a batch: 29 us and 17 us.)
+__device__ __forceinline__ void ph_pyramid(const DevJob &J, int tile)
+{
+    const int lane = threadIdx.x & 63;
+    int u = tile * (kWG / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int per = J.pyr_first[kLevels];
+    const int side = u >= per ? 1 : 0;
+    u -= side * per;
     const FT_G uint8_t *src = side ? J.imgR : J.imgL;
     FT_G uint8_t *dst = side ? J.pyr_outR : J.pyr_outL;
-    if (!src) return;
-    const int Y0 = (tile - side * per) * kPyrRows;
-    const int Y1 = min(Y0 + kPyrRows, H);
-    const int ys = min(Y1 + 1, H);           // staged rows [Y0, ys)
-    const int stride = (W + 3) & ~3;
-    uint8_t *stage = smem;
-    int *meta = reinterpret_cast<int *>(smem + kPyrMeta);          // first row | row count per level
-    uint32_t *rtab = reinterpret_cast<uint32_t *>(smem + kPyrRowTab);
-    const int tid = threadIdx.x;
-    // one thread per (level, row) tap of the tile
-    if (tid < (kLevels - 1) * kPyrRowTaps) {
-        const int l = 1 + tid / kPyrRowTaps, r = tid - (l - 1) * kPyrRowTaps;
-        const int hl = J.lv_h[l];
-        const int ylo = pyr_first_row(Y0, H, hl);
-        const int yhi = Y1 >= H ? hl : pyr_first_row(Y1, H, hl);
-        const int n = min(yhi - ylo, kPyrRowTaps);   // at most ceil(kPyrRows * hl / H) + 1 rows
-        if (r == 0) {
-            meta[2 * l] = ylo;
-            meta[2 * l + 1] = n;
-        }
-        if (r < n) rtab[l * kPyrRowTaps + r] = pyr_tap(ylo + r, H, hl);
-    }
-    // Stage the level-0 rows (4-byte loads when rows and base are aligned).
-    // Element e of a row-major walk is row e / w, column e % w: one division
-    // for the thread's first element, then steps of kWG elements.
-    auto walk = [&](int w, int &r, int &c, int &dr, int &dc) {
-        r = tid / w;
-        c = tid - r * w;
-        dr = kWG / w;
-        dc = kWG - dr * w;
-    };
-    auto step = [&](int w, int &r, int &c, int dr, int dc) {
-        r += dr;
-        c += dc;
-        if (c >= w) {
-            c -= w;
-            ++r;
-        }
-    };
-    const bool al4 = ((reinterpret_cast<uintptr_t>(src) | (uintptr_t)pitch | (uintptr_t)W) & 3u) == 0;
-    if (al4) {
-        const int wq = W >> 2;
-        int r, c, dr, dc;
-        walk(wq, r, c, dr, dc);
-        for (; r < ys - Y0; step(wq, r, c, dr, dc)) {
-            const uint32_t v = *reinterpret_cast<const FT_G uint32_t *>(src + (size_t)(Y0 + r) * pitch + 4 * c);
-            *reinterpret_cast<uint32_t *>(stage + r * stride + 4 * c) = v;
-        }
-    } else {
-        int r, c, dr, dc;
-        walk(W, r, c, dr, dc);
-        for (; r < ys - Y0; step(W, r, c, dr, dc)) stage[r * stride + c] = src[(size_t)(Y0 + r) * pitch + c];
-    }
-    __syncthreads();
-    // level 0: the staged rows [Y0, Y1)
+    if (u >= per || !src) return;
+    const int W = J.img_w, H = J.img_h, pitch = J.img_pitch, rl = J.pyr_rows_log2;
+    int l = 0, first = 0, wl = W, hl = H;
+    int64_t off = 0;
+    _Pragma("unroll") for (int k = 1; k < kLevels; ++k)
     {
-        FT_G uint8_t *d0 = dst + (size_t)Y0 * W;
-        if ((W & 3) == 0 && (reinterpret_cast<uintptr_t>(dst) & 3u) == 0) {
-            const int wq = W >> 2;
-            int r, c, dr, dc;
-            walk(wq, r, c, dr, dc);
-            for (; r < Y1 - Y0; step(wq, r, c, dr, dc))
-                *reinterpret_cast<FT_G uint32_t *>(d0 + (size_t)r * W + 4 * c) =
-                    *reinterpret_cast<const uint32_t *>(stage + r * stride + 4 * c);
-        } else {
-            int r, c, dr, dc;
-            walk(W, r, c, dr, dc);
-            for (; r < Y1 - Y0; step(W, r, c, dr, dc)) d0[(size_t)r * W + c] = stage[r * stride + c];
-        }
+        const bool in = u >= J.pyr_first[k];
+        l = in ? k : l;
+        first = in ? J.pyr_first[k] : first;
+        wl = in ? J.lv_w[k] : wl;
+        hl = in ? J.lv_h[k] : hl;
+        off = in ? J.lv_off[k] : off;
     }
-    // levels 1..7: columns of the levels laid end to end, dealt over the threads
-    int wsum[kLevels];
-    int total = 0;
-    _Pragma("unroll") for (int l = 1; l < kLevels; ++l)
-    {
-        wsum[l] = total;
-        total += J.lv_w[l];
+    // strips of a level column by column
+    const int ny = (hl + (1 << rl) - 1) >> rl;
+    int by = u - first, bx = 0;
+    while (by >= ny) {
+        by -= ny;
+        ++bx;
     }
-    for (int e = tid; e < total; e += kWG) {
-        int l = 1;
-        _Pragma("unroll") for (int k = 2; k < kLevels; ++k) l = e >= wsum[k] ? k : l;
-        const int x = e - wsum[l];
-        const int wl = J.lv_w[l];
-        const uint32_t c = pyr_tap(x, W, wl);
-        // column x0 + 1 is read even where the tap is clamped to the last
-        // column: its weight a is 0 there, and the byte read lies in LDS
-        const int x0 = (int)(c & 0xFFFFu), a = (int)(c >> 16);
-        const int ylo = meta[2 * l], n = meta[2 * l + 1];
-        FT_G uint8_t *dcol = dst + J.lv_off[l] + (size_t)ylo * wl + x;
-        const uint32_t *rt = rtab + l * kPyrRowTaps;
-        for (int r = 0; r < n; ++r) {
-            const uint32_t t = rt[r];
-            const int y0 = (int)(t & 0xFFFFu), b = (int)(t >> 16);
-            const uint8_t *r0 = stage + (y0 - Y0) * stride + x0;
-            const uint8_t *r1 = stage + (min(y0 + 1, H - 1) - Y0) * stride + x0;
-            // (256 - w) p + w q = 256 p + w (q - p), exactly
-            const int p00 = r0[0], p10 = r1[0];
-            const int top = (p00 << 8) + a * ((int)r0[1] - p00);
-            const int bot = (p10 << 8) + a * ((int)r1[1] - p10);
-            const int v = (top << 8) + b * (bot - top);
-            dcol[(size_t)r * wl] = (uint8_t)((v + 32768) >> 16);
-        }
+    const int ylo = by << rl, yhi = min(ylo + (1 << rl), hl);
+    if (l == 0) {
+        pyr_copy(src, W, pitch, dst, bx, ylo, yhi);
+        return;
     }
+    // Every lane stays active (lanes past the last column repeat it and write
+    // nothing): lane r's tap is read by all.
+    const uint32_t taps = pyr_tap(min(ylo + lane, hl - 1), H, hl);   // lane r: output row ylo + r (at most 64 rows)
+    const int x = kPyrStripW * bx + kPyrCols * lane;
+    FT_G uint8_t *out = dst + off;
+    // (column 3's pair ends ceil(3 s) + 1 bytes after the first tap, which is up
+    // to 3 past its dword: 16 bytes while 3 s <= 11; columns 2 and 3 start at
+    // least 4 bytes in from s = 2, column 3 at least 9 from s = 10/3)
+    const bool full = kPyrStripW * (bx + 1) <= wl;
+    // a strip that reads the image's last row (its own last row's taps, or the one
+    // before where the level is as tall as the image) and, with 16 bytes per
+    // lane, past that row's end (the last lane within 24 columns of it)
+    const bool corner = yhi >= hl - 1 && kPyrStripW * (bx + 1) + 20 >= wl;
+    if (corner || W < 16 || 3 * W > 11 * wl) pyr_resample<kAny>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
+    else if (W <= 2 * wl) pyr_resample<kNear>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
+    else if (3 * W <= 10 * wl) pyr_resample<kMid>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
+    else pyr_resample<kFar>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
 }
 
 // ------------------------------------------------ setup: rows (pinhole)
@@ -2175,7 +2295,7 @@ __host__ __device__ inline int final_tiles_view(const DevJob &J, int v)
 void job_tiles(const DevJob &J, const Shapes &s, bool do_stereo, bool do_search, int32_t out[PH_COUNT])
 {
     for (int p = 0; p < PH_COUNT; ++p) out[p] = 0;
-    if (do_stereo && J.imgL) out[PH_PYRAMID] = (J.imgR ? 2 : 1) * div_up(J.img_h, kPyrRows);
+    if (do_stereo && J.imgL) out[PH_PYRAMID] = div_up((J.imgR ? 2 : 1) * J.pyr_first[kLevels], kWG / 64);
     const int nL = J.L.n;
     const bool pin = do_stereo && (J.flags & JOB_STEREO_PINHOLE);
     const bool fish = do_stereo && (J.flags & JOB_STEREO_FISHEYE);
@@ -2305,10 +2425,9 @@ static_assert((256 + kWG + 8) * 4 + (kMaxKp + 32) / 32 * 4 <= kTaskLds, "median 
 template <class Src>
 __global__ __launch_bounds__(kWG) void k_pyramid(Src src)
 {
-    __shared__ __align__(16) unsigned char smem[kPyrLds];
     int job, tile;
     if (!src.locate(PH_PYRAMID, job, tile)) return;
-    ph_pyramid(src(job), tile, smem);
+    ph_pyramid(src(job), tile);
 }
 
 template <class Src, int NT>
