@@ -26,14 +26,21 @@ namespace ft {
 namespace {
 
 constexpr int kThreads = 256;      // description: one wave per keypoint, 4 waves per workgroup
-constexpr int kDetThreads = 1024;  // detection: one tile per workgroup, 4 waves per SIMD
+constexpr int kDetThreads = 512;   // detection: one tile per workgroup, two workgroups per CU
+constexpr int kDetWaves = kDetThreads / 64;
 constexpr int kStaged = kOrbRows + 2 * kOrbHalo;   // level rows staged per tile
 constexpr int kScoreRows = kOrbRows + 2;           // score rows: the tile and one row each side
 static_assert(kOrbRows % 2 == 0 && kOrbRows <= 8 && kMaxPyrW < 2048, "emitted corners pack column, row, score");
 
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef short i16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef v4u v4u_dw __attribute__((aligned(4)));       // four dwords from a dword boundary
+typedef uint32_t u32_any __attribute__((aligned(1)));  // a dword at any byte address
+
 // The 16 ring pixels at distance 3 (clockwise from straight above).
-__constant__ int8_t kRingDx[16] = {0, 1, 2, 3, 3, 3, 2, 1, 0, -1, -2, -3, -3, -3, -2, -1};
-__constant__ int8_t kRingDy[16] = {-3, -3, -2, -1, 0, 1, 2, 3, 3, 3, 2, 1, 0, -1, -2, -3};
+constexpr int kRingDx[16] = {0, 1, 2, 3, 3, 3, 2, 1, 0, -1, -2, -3, -3, -3, -2, -1};
+constexpr int kRingDy[16] = {-3, -3, -2, -1, 0, 1, 2, 3, 3, 3, 2, 1, 0, -1, -2, -3};
 
 __device__ __forceinline__ int level_of_tile(const OrbDetectArgs &a, int tile)
 {
@@ -42,223 +49,301 @@ __device__ __forceinline__ int level_of_tile(const OrbDetectArgs &a, int tile)
     return l;
 }
 
-// FAST-9 score of the staged pixel (x, staged row sr), 0 unless it reaches t.
-__device__ __forceinline__ int fast_score(const unsigned char *px, int S, int sr, int x, int t)
+// Inclusive prefix sum over the 64 lanes of a wave (every lane active) by DPP
+// moves: shifts by 1, 2, 4 and 8 inside rows of 16 lanes, then lane 15 of rows 0
+// and 2 into rows 1 and 3, then lane 31 into rows 2 and 3.
+__device__ __forceinline__ int wave_scan(int v)
 {
-    const unsigned char *p = px + sr * S + x;
-    const int c = p[0];
-    const int hi = c + t, lo = c - t;
-    const int n0 = p[-3 * S], n4 = p[3], n8 = p[3 * S], n12 = p[-3];
-    // nine consecutive ring pixels always include two neighbouring compass points
-    const bool b0 = n0 > hi, b4 = n4 > hi, b8 = n8 > hi, b12 = n12 > hi;
-    const bool d0 = n0 < lo, d4 = n4 < lo, d8 = n8 < lo, d12 = n12 < lo;
-    const bool maybe = (b0 && b4) || (b4 && b8) || (b8 && b12) || (b12 && b0) || (d0 && d4) || (d4 && d8) ||
-                       (d8 && d12) || (d12 && d0);
-    if (!maybe) return 0;
-    int e[16];
-    _Pragma("unroll") for (int k = 0; k < 16; ++k) e[k] = (int)p[kRingDy[k] * S + kRingDx[k]] - c;
-    // sliding minimum (bright side), then maximum (dark side), over nine
-    // consecutive ring pixels by doubling; one side at a time keeps the live
-    // set small
-    int bright = -256, dark = 256;   // best arc minimum; smallest arc maximum
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31
+    return v;
+}
+
+// Sum over the 64 lanes, wave-uniform.
+__device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_scan(v), 63); }
+
+// LDS rows of a level W wide: 4 bytes, the W pixels, at least 8 bytes; whole
+// dwords, so pixel x of a row lies at byte 4 + x and groups of four pixels on
+// dword boundaries.
+__host__ __device__ inline int row_stride(int W) { return (W + 15) & ~3; }
+
+// it / n for 0 <= it < 2^15, 0 < n < 2^11 (inv = 1 / n in binary32): the exact
+// quotient is at least 1 / (2n) away from an integer, far above the rounding.
+__device__ __forceinline__ int div_items(int it, float inv) { return (int)(((float)it + 0.5f) * inv); }
+
+__device__ __forceinline__ u16x2 pk(uint32_t v) { return __builtin_bit_cast(u16x2, v); }
+
+// Bytes j and j + 1 of the twelve in w as a pair of 16-bit values (j constant).
+__device__ __forceinline__ u16x2 byte_pair(const uint32_t w[3], int j)
+{
+    const int k = j < 7 ? j : j - 4;
+    const uint32_t sel = 0x0C000C00u | (uint32_t)k | ((uint32_t)(k + 1) << 16);
+    return pk(j < 7 ? __builtin_amdgcn_perm(w[1], w[0], sel) : __builtin_amdgcn_perm(w[2], w[1], sel));
+}
+
+// Twelve bytes x - 4 .. x + 7 of an LDS row (x a multiple of 4).
+__device__ __forceinline__ void row_window(const unsigned char *row, int x, uint32_t w[3])
+{
+    const uint32_t *q = reinterpret_cast<const uint32_t *>(row + x);   // (the row's pixels start 4 bytes in)
+    w[0] = q[0];
+    w[1] = q[1];
+    w[2] = q[2];
+}
+
+// FAST-9 scores of the four pixels x .. x + 3 whose ring's top row is the LDS
+// row `top`, one byte each: the largest, over the 16 arcs of nine ring pixels,
+// of (smallest ring pixel - centre) and (centre - largest ring pixel), minus
+// one; 0 unless it reaches t.  Two pixels per packed 16-bit operation.  The two
+// arcs that start at ring pixels k and k + 1 share the eight pixels k + 1 ..
+// k + 8, so eight windows of eight pixels (by doubling) and one more pixel from
+// either side give all 16: max(min(m, e[k]), min(m, e[k + 9])) =
+// min(m, max(e[k], e[k + 9])).
+__device__ __forceinline__ uint32_t fast_scores(const unsigned char *top, int S, int x, uint32_t t)
+{
+    uint32_t w[7][3];
+    _Pragma("unroll") for (int r = 0; r < 7; ++r) row_window(top + r * S, x, w[r]);
+    uint32_t out[2];
+    _Pragma("unroll") for (int h = 0; h < 2; ++h)
     {
-        int a2[16], a4[16];
-        _Pragma("unroll") for (int k = 0; k < 16; ++k) a2[k] = min(e[k], e[(k + 1) & 15]);
-        _Pragma("unroll") for (int k = 0; k < 16; ++k) a4[k] = min(a2[k], a2[(k + 2) & 15]);
-        _Pragma("unroll") for (int k = 0; k < 16; ++k)
-            bright = max(bright, min(min(a4[k], a4[(k + 4) & 15]), e[(k + 8) & 15]));
-    }
-    {
-        int a2[16], a4[16];
-        _Pragma("unroll") for (int k = 0; k < 16; ++k) a2[k] = max(e[k], e[(k + 1) & 15]);
-        _Pragma("unroll") for (int k = 0; k < 16; ++k) a4[k] = max(a2[k], a2[(k + 2) & 15]);
-        _Pragma("unroll") for (int k = 0; k < 16; ++k)
-            dark = min(dark, max(max(a4[k], a4[(k + 4) & 15]), e[(k + 8) & 15]));
-    }
-    const int s = max(bright, -dark) - 1;
-    return s >= t ? s : 0;
-}
-
-// Stage the tile's level rows (clamped at the level's borders) into LDS with
-// row stride W, and fill the score band (stride W); returns after a barrier.
-// `lds` is 16-byte aligned; the staged rows start at the returned pointer.
-// Interior tiles copy one contiguous range: aligned dwords (every load issued
-// before the LDS stores), bytes at the two ragged ends; a tile whose halo
-// leaves the level copies row by row with clamped row indices.
-__device__ __forceinline__ unsigned char *stage_and_score(const OrbDetectArgs &a, int l, int y0, int rows,
-                                                          unsigned char *lds)
-{
-    const int W = a.w[l], H = a.h[l];
-    const FT_G uint8_t *img = a.pyr + a.off[l];
-    const int n_staged = rows + 2 * kOrbHalo;
-    unsigned char *px;
-    if (y0 - kOrbHalo >= 0 && y0 + rows + kOrbHalo <= H) {
-        const FT_G uint8_t *g0 = img + (int64_t)(y0 - kOrbHalo) * W;
-        const int len = n_staged * W;
-        const uintptr_t ga = reinterpret_cast<uintptr_t>(g0);
-        const int sh = (int)(ga & 3u);
-        px = lds + sh;                                   // px[i] = g0[i]; aligned dwords land aligned
-        const int head = sh ? 4 - sh : 0;                // bytes before the first aligned dword
-        const int nd = (len - head) >> 2;                // whole aligned dwords
-        const FT_G uint32_t *gd = reinterpret_cast<const FT_G uint32_t *>(g0 + head);
-        uint32_t *ld = reinterpret_cast<uint32_t *>(px + head);
-        constexpr int kMaxPer = (kStaged * kMaxPyrW / 4 + kDetThreads - 1) / kDetThreads;
-        uint32_t v[kMaxPer];
-        _Pragma("unroll") for (int k = 0; k < kMaxPer; ++k)
+        u16x2 e[16];
+        _Pragma("unroll") for (int k = 0; k < 16; ++k) e[k] = byte_pair(w[3 + kRingDy[k]], 4 + 2 * h + kRingDx[k]);
+        const u16x2 c = byte_pair(w[3], 4 + 2 * h);
+        auto lo = [](u16x2 a, u16x2 b) { return __builtin_elementwise_min(a, b); };
+        auto hi = [](u16x2 a, u16x2 b) { return __builtin_elementwise_max(a, b); };
+        u16x2 bright = {0, 0}, dark = {255, 255};   // best arc minimum; smallest arc maximum
         {
-            const int j = (int)threadIdx.x + k * kDetThreads;
-            if (j < nd) v[k] = gd[j];
+            u16x2 a2[16], a4[16];
+            _Pragma("unroll") for (int k = 1; k < 16; k += 2) a2[k] = lo(e[k], e[(k + 1) & 15]);
+            _Pragma("unroll") for (int k = 1; k < 16; k += 2) a4[k] = lo(a2[k], a2[(k + 2) & 15]);
+            _Pragma("unroll") for (int k = 1; k < 16; k += 2)
+                bright = hi(bright, lo(lo(a4[k], a4[(k + 4) & 15]), hi(e[k - 1], e[(k + 8) & 15])));
         }
-        _Pragma("unroll") for (int k = 0; k < kMaxPer; ++k)
         {
-            const int j = (int)threadIdx.x + k * kDetThreads;
-            if (j < nd) ld[j] = v[k];
+            u16x2 a2[16], a4[16];
+            _Pragma("unroll") for (int k = 1; k < 16; k += 2) a2[k] = hi(e[k], e[(k + 1) & 15]);
+            _Pragma("unroll") for (int k = 1; k < 16; k += 2) a4[k] = hi(a2[k], a2[(k + 2) & 15]);
+            _Pragma("unroll") for (int k = 1; k < 16; k += 2)
+                dark = lo(dark, hi(hi(a4[k], a4[(k + 4) & 15]), lo(e[k - 1], e[(k + 8) & 15])));
         }
-        const int tail0 = head + 4 * nd;
-        if ((int)threadIdx.x < head) px[threadIdx.x] = g0[threadIdx.x];
-        if ((int)threadIdx.x < len - tail0) px[tail0 + threadIdx.x] = g0[tail0 + threadIdx.x];
-    } else {
-        px = lds;
-        for (int sr = 0; sr < n_staged; ++sr) {
-            int yy = y0 - kOrbHalo + sr;
-            yy = yy < 0 ? 0 : (yy > H - 1 ? H - 1 : yy);
-            const FT_G uint8_t *src = img + (int64_t)yy * W;
-            for (int x = threadIdx.x; x < W; x += kDetThreads) px[sr * W + x] = src[x];
-        }
+        const i16x2 d = __builtin_elementwise_max(__builtin_bit_cast(i16x2, (u16x2)(bright - c)),
+                                                  __builtin_bit_cast(i16x2, (u16x2)(c - dark)));
+        // d = score + 1 >= t + 1, else 0 (t < 255, so t + 1 fits)
+        const u16x2 sp = __builtin_bit_cast(u16x2, __builtin_elementwise_max(d, i16x2{0, 0}));
+        const u16x2 over = __builtin_elementwise_sub_sat(sp, u16x2{(unsigned short)t, (unsigned short)t});
+        const u16x2 keep = __builtin_elementwise_min(over, u16x2{1, 1});
+        out[h] = __builtin_bit_cast(uint32_t, (u16x2)((sp - keep) * keep));
     }
-    __syncthreads();
-    const int S = W;
-    unsigned char *sc = lds + 4 + kStaged * a.lds_w;    // after the staged rows and their slack
-    const int E = a.edge;
-    for (int r = 0; r < rows + 2; ++r) {
-        const int yy = y0 - 1 + r;
-        const bool row_in = yy >= E && yy < H - E;
-        for (int x = threadIdx.x; x < W; x += kDetThreads) {
-            int s = 0;
-            if (row_in && x >= E && x < W - E) s = fast_score(px, S, r + kOrbHalo - 1, x, a.t);
-            sc[r * S + x] = (unsigned char)s;
-        }
-    }
-    __syncthreads();
-    return px;
+    return __builtin_amdgcn_perm(out[1], out[0], 0x06040200u);
 }
 
-__device__ __forceinline__ unsigned char *score_band(const OrbDetectArgs &a, unsigned char *lds)
-{
-    return lds + 4 + kStaged * a.lds_w;
-}
-
-// A tile's kept corners (emission): strict suppression never keeps two
-// 8-neighbours, so a tile holds at most (kOrbRows / 2) x ceil(W / 2) corners;
-// lds_w is W rounded up to 4, so (kOrbRows / 2) x (lds_w / 2) entries suffice.
-__device__ __forceinline__ uint32_t *corner_list(const OrbDetectArgs &a, unsigned char *lds)
-{
-    return reinterpret_cast<uint32_t *>(lds + 8 + (kStaged + kScoreRows) * a.lds_w);
-}
-
-// Is the corner at output row r, column x kept by the suppression?
-__device__ __forceinline__ bool kept(const unsigned char *sc, int S, int r, int x, int W)
-{
-    if (x >= W) return false;
-    const unsigned char *q = sc + (r + 1) * S + x;
-    const int v = q[0];
-    if (v == 0) return false;
-    // window pixels are >= 19 from every border: the 8 neighbours exist
-    return v > q[-S - 1] && v > q[-S] && v > q[-S + 1] && v > q[-1] && v > q[1] && v > q[S - 1] && v > q[S] &&
-           v > q[S + 1];
-}
-
-constexpr int kDetWaves = kDetThreads / 64;
-
-// Look-back state of a tile: epoch << 32 | flag << 30 | value (corners).
-constexpr unsigned long long kAggregate = 1ull << 30, kInclusive = 2ull << 30;
+// Look-back state of a tile: epoch << 32 | published << 30 | corners.
+constexpr unsigned long long kPublished = 1ull << 30;
 constexpr uint32_t kValueMask = (1u << 30) - 1u;
 constexpr int kMaxSpins = 1 << 16;       // bounds every wait (a tile found stuck poisons the prefix)
 constexpr int kPoison = 1 << 29;         // prefix of a tile whose predecessors never published
 
-__global__ __launch_bounds__(kDetThreads, 8) void k_orb_detect(OrbDetectArgs a)
+// One tile.  What bounds it is the chain ticket, staging, scores, suppression,
+// look-back, output of a single tile (277 tiles of a 752x480 pyramid on 256
+// CUs, one round), so the work per pixel is cut where it is vector issue: four
+// pixels per lane from dword LDS reads, two per packed 16-bit operation (about
+// 60 instructions per pixel against 220 one pixel at a time), the smoothing by
+// byte dot products, and the tile's count is published before the smoothing so
+// that the other tiles' counts arrive meanwhile.
+__global__ __launch_bounds__(kDetThreads, 4) void k_orb_detect(OrbDetectArgs a)
 {
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ int wave_n[kDetWaves];
-    __shared__ int shared_tile, shared_prefix;
+    constexpr int kItems = (kOrbRows * ((kMaxPyrW + 3) / 4) + kDetThreads - 1) / kDetThreads;   // four-pixel items per thread
+    static_assert(kItems * kDetWaves <= 64, "one lane per (round, wave) count");
+    __shared__ int wave_n[kItems * kDetWaves];
+    __shared__ int shared_tile, wave_prefix[kDetWaves];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     // tiles by ticket: every lower tile has been taken by a running workgroup,
     // and none waits on a higher one, so each wait below ends
-    if (threadIdx.x == 0) shared_tile = (int)(atomicAdd(a.ticket, 1u) - a.ticket_base);
+    if (tid == 0) shared_tile = (int)(atomicAdd(a.ticket, 1u) - a.ticket_base);
+    if (tid < kItems * kDetWaves) wave_n[tid] = 0;
     __syncthreads();
-    const int tile = shared_tile;
+    const int tile = __builtin_amdgcn_readfirstlane(shared_tile);
     const int tiles = a.tile0[kLevels];
     const int l = level_of_tile(a, tile);
-    const int W = a.w[l], H = a.h[l], S = W;
+    const int W = a.w[l], H = a.h[l], S = row_stride(W), E = a.edge;
     const int y0 = (tile - a.tile0[l]) * kOrbRows;
     const int rows = min(kOrbRows, H - y0);
-    const unsigned char *px = stage_and_score(a, l, y0, rows, lds);
-    const unsigned char *sc = score_band(a, lds);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const unsigned long long ep = (unsigned long long)a.epoch << 32;
-    // the tile's corners in (row, column) order, packed column | row << 11 |
-    // score << 14
-    uint32_t *tc = corner_list(a, lds);
-    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-    int n = 0;
-    for (int r = 0; r < rows; ++r)
-        for (int x0 = 0; x0 < W; x0 += kDetThreads) {
-            const int x = x0 + (int)threadIdx.x;
-            const bool k = kept(sc, S, r, x, W);
-            const uint64_t m = __ballot(k);
-            if (lane == 0) wave_n[wave] = __popcll(m);
-            __syncthreads();
-            int off = n;
-            for (int w = 0; w < wave; ++w) off += wave_n[w];
-            int chunk = 0;
-            _Pragma("unroll") for (int w = 0; w < kDetWaves; ++w) chunk += wave_n[w];
-            __syncthreads();
-            if (k) tc[off + __popcll(m & below)] = (uint32_t)x | ((uint32_t)r << 11) | ((uint32_t)sc[(r + 1) * S + x] << 14);
-            n += chunk;
-        }
-    // decoupled look-back: the tile publishes its count; wave 0 then reads 64
-    // predecessors' states at a time and adds the counts down to the nearest
-    // inclusive prefix (a window with an unpublished state before it is read
-    // again); the tile then publishes its own inclusive prefix
-    if (wave == 0) {
-        int prefix = 0;
-        if (lane == 0)
-            atomicExch(&a.tile_state[tile], ep | (tile == 0 ? kInclusive : kAggregate) | (unsigned long long)n);
-        if (tile > 0) {
-            int top = tile - 1, spins = 0;
-            for (;;) {
-                const int k = top - lane;
-                unsigned long long v = ep | kInclusive;          // before tile 0: an inclusive 0
-                if (k >= 0) v = atomicOr(&a.tile_state[k], 0ull);  // coherent read
-                const bool pub = (v >> 32) == a.epoch && (v & (3ull << 30));
-                const uint64_t inc = __ballot(pub && (v & kInclusive));
-                const uint64_t unpub = __ballot(!pub);
-                const int first = inc ? __ffsll((long long)inc) - 1 : 64;   // nearest inclusive lane
-                const uint64_t upto = first == 64 ? ~0ull : (~0ull >> (63 - first));
-                if (unpub & upto) {
-                    if (++spins > kMaxSpins) {
-                        prefix += kPoison;
-                        break;
-                    }
-                    continue;
+    unsigned char *px = lds;                                // staged rows
+    unsigned char *sc = lds + kStaged * row_stride(a.lds_w);  // scores: rows y0 - 1 .. y0 + rows
+    uint32_t *tc = reinterpret_cast<uint32_t *>(sc + kScoreRows * row_stride(a.lds_w));
+    const FT_G uint8_t *img = a.pyr + a.off[l];
+    // Stage rows y0 - 4 .. y0 + rows + 3 (clamped), each from 4 pixels before
+    // its first to 8 past its last (clamped), as dwords realigned from the
+    // level's (every dword read holds a byte of the row); the ones that hold a
+    // clamped pixel byte by byte.
+    {
+        const int nd = S >> 2, n = (rows + 2 * kOrbHalo) * nd;
+        const float inv = 1.0f / (float)nd;
+        constexpr int kPer = (kStaged * ((kMaxPyrW + 15) / 4) + kDetThreads - 1) / kDetThreads;
+        constexpr int kBatch = 4;   // dwords per thread whose loads are issued together
+        for (int k0 = 0; k0 < kPer; k0 += kBatch) {
+            if (k0 * kDetThreads >= n) break;
+            uint32_t v[kBatch];
+            _Pragma("unroll") for (int k = 0; k < kBatch; ++k)
+            {
+                const int it = min((k0 + k) * kDetThreads + tid, n - 1);
+                const int sr = div_items(it, inv), x = 4 * (it - sr * nd) - 4;
+                const int yy = min(max(y0 - kOrbHalo + sr, 0), H - 1);
+                const FT_G uint8_t *row = img + (int64_t)yy * W;
+                if (x >= 0 && x + 4 <= W) {
+                    const uint32_t sh = (uint32_t)reinterpret_cast<uintptr_t>(row + x) & 3u;
+                    const FT_G uint32_t *q = reinterpret_cast<const FT_G uint32_t *>(row + x - sh);
+                    v[k] = __builtin_amdgcn_alignbyte(q[sh ? 1 : 0], q[0], sh);
+                } else {
+                    uint32_t e[4];
+                    _Pragma("unroll") for (int j = 0; j < 4; ++j) e[j] = row[min(max(x + j, 0), W - 1)];
+                    v[k] = e[0] | (e[1] << 8) | (e[2] << 16) | (e[3] << 24);
                 }
-                int add = (lane <= first) ? (int)(v & kValueMask) : 0;
-                _Pragma("unroll") for (int o = 32; o > 0; o >>= 1) add += __shfl_xor(add, o);
-                prefix += add;
-                if (first < 64) break;
-                top -= 64;
             }
-            if (lane == 0)
-                atomicExch(&a.tile_state[tile], ep | kInclusive | (unsigned long long)min(prefix + n, (int)kValueMask));
-        }
-        if (lane == 0) {
-            shared_prefix = prefix;
-            if (tile == tiles - 1) a.count[0] = prefix + n >= kPoison ? -1 : prefix + n;
+            _Pragma("unroll") for (int k = 0; k < kBatch; ++k)
+            {
+                const int it = (k0 + k) * kDetThreads + tid;
+                if (it < n) reinterpret_cast<uint32_t *>(px)[it] = v[k];
+            }
         }
     }
     __syncthreads();
-    const int before = shared_prefix;
+    const int G = (W + 3) >> 2;            // four-pixel groups of a row
+    const float inv_g = 1.0f / (float)G;
+    for (int it = tid; it < (rows + 2) * G; it += kDetThreads) {
+        const int r = div_items(it, inv_g), x = 4 * (it - r * G);
+        const int yy = y0 - 1 + r;
+        uint32_t s4 = 0;
+        if (yy >= E && yy < H - E && x + 3 >= E && x < W - E) {
+            s4 = fast_scores(px + r * S, S, x, (uint32_t)a.t);
+            // pixels of the window only
+            _Pragma("unroll") for (int j = 0; j < 4; ++j)
+                if (x + j < E || x + j >= W - E) s4 &= ~(0xFFu << (8 * j));
+        }
+        *reinterpret_cast<uint32_t *>(sc + r * S + 4 + x) = s4;
+    }
+    __syncthreads();
+    // strict suppression (a group's window pixels lie >= 19 from every border,
+    // so what the band's row ends hold never matters); the kept corners of
+    // round k of this thread as four bits and the counts of every wave
+    uint32_t kept[kItems], cen[kItems];
+    const uint64_t below = (1ull << lane) - 1ull;
+    int rank[kItems];
+    _Pragma("unroll") for (int k = 0; k < kItems; ++k)
+    {
+        kept[k] = cen[k] = 0;
+        rank[k] = 0;
+        if (k * kDetThreads >= rows * G) continue;   // (uniform)
+        const int it = k * kDetThreads + tid;
+        if (it < rows * G) {
+            const int r = div_items(it, inv_g), x = 4 * (it - r * G);
+            uint32_t w[3][3];
+            _Pragma("unroll") for (int d = 0; d < 3; ++d) row_window(sc + (r + d) * S, x, w[d]);
+            cen[k] = w[1][1];
+            _Pragma("unroll") for (int h = 0; h < 2; ++h)
+            {
+                u16x2 m = byte_pair(w[1], 3 + 2 * h);
+                m = __builtin_elementwise_max(m, byte_pair(w[1], 5 + 2 * h));
+                _Pragma("unroll") for (int d = 0; d < 3; d += 2)
+                    _Pragma("unroll") for (int j = 3; j < 6; ++j) m = __builtin_elementwise_max(m, byte_pair(w[d], j + 2 * h));
+                const u16x2 over = __builtin_elementwise_sub_sat(byte_pair(w[1], 4 + 2 * h), m);
+                kept[k] |= (over[0] ? 1u : 0u) << (2 * h) | (over[1] ? 2u : 0u) << (2 * h);
+            }
+        }
+        const int cnt = __popc(kept[k]);             // 0, 1 or 2 (no two neighbours)
+        const uint64_t m1 = __ballot(cnt & 1), m2 = __ballot(cnt & 2);
+        rank[k] = __popcll(m1 & below) + 2 * __popcll(m2 & below);
+        if (lane == 0) wave_n[k * kDetWaves + wave] = __popcll(m1) + 2 * __popcll(m2);
+    }
+    __syncthreads();
+    int n;
+    {
+        int v = lane < kItems * kDetWaves ? wave_n[lane] : 0;
+        v = wave_scan(v);
+        n = __builtin_amdgcn_readlane(v, 63);
+        _Pragma("unroll") for (int k = 0; k < kItems; ++k)
+        {
+            const int j = k * kDetWaves + __builtin_amdgcn_readfirstlane(wave);
+            rank[k] += j ? __builtin_amdgcn_readlane(v, (j - 1) & 63) : 0;
+        }
+    }
+    // the tile's count, before anything that does not depend on the others
+    const unsigned long long ep = (unsigned long long)a.epoch << 32;
+    if (tid == 0)
+        __hip_atomic_store(&a.tile_state[tile], ep | kPublished | (unsigned long long)n, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    // the tile's corners in (row, column) order: column | row << 11 | score << 14
+    _Pragma("unroll") for (int k = 0; k < kItems; ++k)
+    {
+        if (k * kDetThreads >= rows * G) continue;
+        const int it = k * kDetThreads + tid;
+        const int r = div_items(it, inv_g), x = 4 * (it - r * G);
+        int at = rank[k];
+        _Pragma("unroll") for (int j = 0; j < 4; ++j)
+            if ((kept[k] >> j) & 1u)
+                tc[at++] = (uint32_t)(x + j) | ((uint32_t)r << 11) | (((cen[k] >> (8 * j)) & 0xFFu) << 14);
+    }
+    if (a.blurred) {
+        // Smoothing, four columns by two rows per item: horizontal sums of the
+        // eight staged rows by byte dot products, then the vertical taps.
+        FT_G uint8_t *dst = a.blurred + a.off[l];
+        const int pairs = (rows + 1) >> 1;
+        for (int it = tid; it < pairs * G; it += kDetThreads) {
+            const int rp = div_items(it, inv_g), x = 4 * (it - rp * G), r0 = 2 * rp;
+            uint32_t hs[8][4];
+            _Pragma("unroll") for (int k = 0; k < 8; ++k)
+            {
+                uint32_t w[3];
+                row_window(px + (r0 + k + 1) * S, x, w);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j)
+                {
+                    // bytes x + j - 3 .. x + j and x + j + 1 .. x + j + 4
+                    const uint32_t p = j < 3 ? __builtin_amdgcn_alignbyte(w[1], w[0], 1 + j) : w[1];
+                    const uint32_t q = j < 3 ? __builtin_amdgcn_alignbyte(w[2], w[1], 1 + j) : w[2];
+                    hs[k][j] = __builtin_amdgcn_udot4(p, 0x140F0601u, __builtin_amdgcn_udot4(q, 0x0001060Fu, 0u, false), false);
+                }
+            }
+            _Pragma("unroll") for (int r = 0; r < 2; ++r)
+            {
+                if (r0 + r >= rows) break;
+                uint32_t o[4];
+                _Pragma("unroll") for (int j = 0; j < 4; ++j)
+                    o[j] = (hs[r][j] + hs[r + 6][j] + 6u * (hs[r + 1][j] + hs[r + 5][j]) + 15u * (hs[r + 2][j] + hs[r + 4][j]) +
+                            20u * hs[r + 3][j] + 2048u) >> 12;
+                const uint32_t v = o[0] | (o[1] << 8) | (o[2] << 16) | (o[3] << 24);
+                FT_G uint8_t *d = dst + (int64_t)(y0 + r0 + r) * W + x;
+                if (x + 4 <= W) {
+                    *reinterpret_cast<FT_G u32_any *>(d) = v;
+                } else {
+                    _Pragma("unroll") for (int j = 0; j < 3; ++j) if (x + j < W) d[j] = (uint8_t)(v >> (8 * j));
+                }
+            }
+        }
+    }
+    // Look-back: the counts of every lower tile, one per thread and round (each
+    // state is one self-contained 64-bit word, so no other ordering is needed).
+    int prefix = 0;
+    for (int k = tid; k < tile; k += kDetThreads) {
+        unsigned long long v;
+        int spins = 0;
+        do
+            v = __hip_atomic_load(&a.tile_state[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        while (!((v >> 32) == a.epoch && (v & kPublished)) && ++spins <= kMaxSpins);
+        prefix = min(prefix + (spins > kMaxSpins ? kPoison : (int)(v & kValueMask)), kPoison);
+    }
+    // (at most 2^29 + 2^29 per addition: clamped to the poison value before each)
+    _Pragma("unroll") for (int o = 32; o > 0; o >>= 1) prefix = min(prefix + __shfl_xor(prefix, o), kPoison);
+    if (lane == 0) wave_prefix[wave] = prefix;
+    __syncthreads();
+    int before = 0;
+    _Pragma("unroll") for (int w = 0; w < kDetWaves; ++w) before = min(before + wave_prefix[w], kPoison);
+    if (tid == 0 && tile == tiles - 1) a.count[0] = before >= kPoison ? -1 : before + n;
     const float sf = a.sf[l];
-    for (int k = threadIdx.x; k < n; k += kDetThreads) {
+    for (int k = tid; k < n; k += kDetThreads) {
         const int i = before + k;
         if (i >= a.capacity) break;
         const uint32_t e = tc[k];
@@ -269,36 +354,6 @@ __global__ __launch_bounds__(kDetThreads, 8) void k_orb_detect(OrbDetectArgs a)
         a.score[i] = (uint8_t)(e >> 14);
         a.x[i] = (float)x * sf;
         a.y[i] = (float)yy * sf;
-    }
-    if (a.blurred) {
-        // smoothing: per column, horizontal sums of staged rows 1 .. rows + 6
-        // (level rows y0 - 3 .. y0 + rows + 2, clamped), then the vertical taps
-        FT_G uint8_t *dst = a.blurred + a.off[l];
-        constexpr int kw[7] = {1, 6, 15, 20, 15, 6, 1};
-        for (int x = threadIdx.x; x < W; x += kDetThreads) {
-            int xs[7];
-            _Pragma("unroll") for (int i = 0; i < 7; ++i)
-            {
-                const int v = x + i - 3;
-                xs[i] = v < 0 ? 0 : (v > W - 1 ? W - 1 : v);
-            }
-            int hs[kOrbRows + 6];
-            _Pragma("unroll") for (int k = 0; k < kOrbRows + 6; ++k)
-            {
-                const unsigned char *row = px + (k + 1) * S;
-                int acc = 0;
-                _Pragma("unroll") for (int i = 0; i < 7; ++i) acc += kw[i] * row[xs[i]];
-                hs[k] = acc;
-            }
-            _Pragma("unroll") for (int r = 0; r < kOrbRows; ++r)
-            {
-                if (r < rows) {
-                    int acc = 0;
-                    _Pragma("unroll") for (int j = 0; j < 7; ++j) acc += kw[j] * hs[r + j];
-                    dst[(int64_t)(y0 + r) * W + x] = (uint8_t)((acc + 2048) >> 12);
-                }
-            }
-        }
     }
 }
 
@@ -330,20 +385,6 @@ __device__ __forceinline__ int turn_fast(int num, float inv_r, bool &near)
     near |= !(fabsf(fr - 0.5f) > 1e-4f);
     const int k = (int)(q + 0.5f);
     return num < 0 ? -k : k;
-}
-
-// Sum over the 64 lanes of a wave (every lane active) by DPP moves: shifts
-// by 1, 2, 4 and 8 inside rows of 16 lanes, then lane 15 of rows 0 and 2 into
-// rows 1 and 3, then lane 31 into rows 2 and 3; lane 63 holds the total.
-__device__ __forceinline__ int wave_sum(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31
-    return __builtin_amdgcn_readlane(v, 63);
 }
 
 __device__ __forceinline__ float angle_deg(int m10, int m01)
@@ -465,7 +506,9 @@ __global__ __launch_bounds__(kThreads, 4) void k_orb_describe(OrbDescribeArgs a)
 
 size_t orb_detect_lds(int lds_w)
 {
-    return (size_t)(kStaged + kScoreRows) * (size_t)lds_w + 8 + 4 * (size_t)(kOrbRows / 2) * (size_t)(lds_w / 2);
+    // staged rows, scores, and the tile's kept corners: strict suppression never
+    // keeps two 8-neighbours, so at most (kOrbRows / 2) x ceil(W / 2) of them
+    return (size_t)(kStaged + kScoreRows) * (size_t)row_stride(lds_w) + 4 * (size_t)(kOrbRows / 2) * (size_t)(lds_w / 2);
 }
 
 hipError_t launch_orb_detect(const OrbDetectArgs &a, hipStream_t s)
