@@ -2,21 +2,24 @@
 // are extracted on every scale and described; Section IV-B: the extraction
 // runs next to the pyramid on the device).
 //
-//  * k_orb_detect: one 1024-thread workgroup per tile of kOrbRows rows of one
-//    level.  The tile's level rows and kOrbHalo rows above and below are
-//    staged in LDS; FAST-9 scores (a compass-point quick test first) fill a
-//    score band one row larger on each side; strict 3x3 suppression collects
-//    the tile's corners in (row, column) order in LDS; the tile's first output
-//    index comes from a decoupled look-back over the counts of the tiles
-//    before it (tiles are in (level, row) order and taken by ticket), and the
-//    corners are written contiguously; the descriptor's binomial smoothing of
-//    the tile's rows is written from the same staged rows.
+//  * k_orb_detect: one workgroup per tile of kOrbRows rows of one level.  The
+//    tile's level rows and kOrbHalo rows above and below are staged in LDS;
+//    FAST-9 scores, four pixels per lane, fill a score band one row larger on
+//    each side; strict 3x3 suppression collects the tile's corners in (row,
+//    column) order in LDS; the tile publishes its count, and its first output
+//    index is the sum of the counts of the tiles before it (tiles are in (level,
+//    row) order and taken by ticket), so the corners are written contiguously;
+//    the descriptor's binomial smoothing of the tile's rows is written from the
+//    same staged rows.
 //  * k_orb_describe: one wave per keypoint: the intensity-centroid moments
-//    over the radius-15 disc (lanes stride the disc, one wave reduction), then
-//    four tests per lane on the smoothed level with the pattern turned exactly
+//    over the radius-15 disc (byte dot products, one wave reduction), then four
+//    tests per lane on the smoothed window in LDS with the pattern turned exactly
 //    by the moments (integer rounding decisions), and one ballot per 64 tests
 //    gives 8 descriptor bytes.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <climits>
 
 #define FT_KERNELS 1
 #include "ft_internal.h"
@@ -371,20 +374,12 @@ __device__ __forceinline__ int round_ratio_exact(int num, int64_t m2)
     return num < 0 ? -k : k;
 }
 
-// The same integer from a binary32 estimate |num| * rsqrt(m10^2 + m01^2),
-// the squares summed in binary32: every step is within a few units in the
-// last place, and turned pattern coordinates are at most 13, so the estimate
-// is within 1e-5 of the exact quotient and, unless it lies within 1e-4 of a
-// half, rounds to the exact integer; `near` is set otherwise (the caller then
-// decides exactly).
-__device__ __forceinline__ int turn_fast(int num, float inv_r, bool &near)
+// Orders one wave's LDS accesses (its lanes read what other lanes wrote).
+__device__ __forceinline__ void wave_lds_sync()
 {
-    const int a = num < 0 ? -num : num;
-    const float q = (float)a * inv_r;
-    const float fr = q - floorf(q);
-    near |= !(fabsf(fr - 0.5f) > 1e-4f);
-    const int k = (int)(q + 0.5f);
-    return num < 0 ? -k : k;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 __device__ __forceinline__ float angle_deg(int m10, int m01)
@@ -394,112 +389,250 @@ __device__ __forceinline__ float angle_deg(int m10, int m01)
     return (float)ang;
 }
 
-// Four waves per SIMD (at most 128 registers): a few values spill, but the
-// extra waves hide more of the pixel gathers than the spills cost.
+constexpr int kDescSlots = 16;        // most keypoints of a wave (its workgroup's angles: one per lane of a wave)
+constexpr int kDescWaves = kThreads / 64;
+constexpr int kTurnR = 13;            // turned pattern points lie within radius 13
+constexpr int kWinRows = 2 * kTurnR + 1, kWinStride = 32;   // the smoothed window in LDS
+static_assert(kDescSlots * kDescWaves == 64 && kWinRows * 2 <= 64, "one lane per angle and per window half row");
+
+// The disc dx^2 + dy^2 <= 225 over the lanes of a wave: lane = (row dy, half of
+// the 29 columns -14 .. 14), 16 or 13 columns each, and the two pixels (-15, 0)
+// and (15, 0) in lanes 62 and 63 (no other row reaches column 15).  Per lane the
+// column weights dx and the 0 / 1 weights of its 16 bytes.
+struct DiscWeights {
+    uint32_t v[64][8];
+    constexpr DiscWeights() : v{}
+    {
+        for (int lane = 0; lane < 62; ++lane) {
+            const int dy = (lane >> 1) - 15;
+            for (int c = 0; c < 16; ++c) {
+                const int dx = (lane & 1 ? 2 : -14) + c;
+                if (dx > 14 || dx * dx + dy * dy > 225) continue;
+                v[lane][c >> 2] |= ((uint32_t)dx & 0xFFu) << (8 * (c & 3));
+                v[lane][4 + (c >> 2)] |= 1u << (8 * (c & 3));
+            }
+        }
+        v[62][0] = (uint32_t)-15 & 0xFFu;
+        v[63][0] = 15u;
+    }
+};
+__constant__ const DiscWeights kDisc;
+
+// One wave per keypoint.  Both windows are read as aligned dwordx4 (misaligned
+// vector loads take one lane per cycle) and realigned in registers, a half
+// row's last bytes coming from the other half's lane:
+//  * the disc: moments by byte dot products with the lane's column weights
+//    (signed, on pixel - 128: the weights of a row of the disc cancel) and 0 / 1
+//    weights;
+//  * the 27 smoothed rows that turned points can reach, staged in LDS, where the
+//    tests' 512 pixels per keypoint are gathered.
+// The next keypoint's loads are issued before the current one's arithmetic.
+// What bounds it is vector issue (about 240 instructions per keypoint against 600
+// one byte load per disc pixel and one gather from memory per test point: 76 ->
+// 36 us at 47,700 keypoints), then the window rows' trips through L1.
 __global__ __launch_bounds__(kThreads, 4) void k_orb_describe(OrbDescribeArgs a)
 {
+    __shared__ __align__(16) unsigned char win[kDescWaves * 64 * 16];
+    __shared__ float4 pattern[kOrbTests];
+    __shared__ int list_i[64], list_m10[64], list_m01[64];
+    static_assert(kOrbTests == kThreads, "a test per thread");
     const int lane = threadIdx.x & 63;
-    const int wave = (int)((blockIdx.x * kThreads + threadIdx.x) >> 6);
-    const int waves = (int)(gridDim.x * (kThreads / 64));
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wave = (int)blockIdx.x * kDescWaves + w;
+    const int waves = (int)gridDim.x * kDescWaves;
     int n = a.n_max;
     if (a.count) {
         const int c = a.count[0];
         n = c < n ? c : n;
     }
-    // this lane's four tests (t = 64 q + lane), held for the whole kernel
-    int tx1[4], ty1[4], tx2[4], ty2[4];
-    _Pragma("unroll") for (int q = 0; q < 4; ++q)
+    if ((int)blockIdx.x * kDescWaves >= n) return;
+    // slot s is keypoint s * waves + wave; lane s reads its record
+    const int mine = (lane & (kDescSlots - 1)) * waves + wave;
+    const int rec = min(mine, n - 1);
+    const int l = a.oct[rec], u = a.lx[rec], v = a.ly[rec];
+    // the tests' points
     {
-        const int t = q * 64 + lane;
-        tx1[q] = a.pattern[t][0];
-        ty1[q] = a.pattern[t][1];
-        tx2[q] = a.pattern[t][2];
-        ty2[q] = a.pattern[t][3];
+        const int t = (int)threadIdx.x;
+        pattern[t] = make_float4((float)a.pattern[t][0], (float)a.pattern[t][1], (float)a.pattern[t][2], (float)a.pattern[t][3]);
+        __syncthreads();
     }
-    // disc geometry of this lane: column dx for all 16 positions, rows dy0 + 2j
-    const int dx = (lane & 31) - 15, dxl = dx < 15 ? dx : 15;
-    const int dy0 = (lane >> 5) - 15;
-    // angles: lane (slot % 64) keeps the moments of the wave's slot-th
-    // keypoint; every 64 slots (and at the end) each lane converts its own
-    int keep_i = -1, keep_m10 = 0, keep_m01 = 0;
-    int slot = 0;
-    for (int i = wave; i < n; i += waves, ++slot) {
-        const int l = a.oct[i];
-        const int u = a.lx[i], v = a.ly[i];
-        const bool ok = l < kLevels && u >= 15 && v >= 15 && u < a.w[l < kLevels ? l : 0] - 15 &&
-                        v < a.h[l < kLevels ? l : 0] - 15;
+    uint32_t wdx[4], wone[4];
+    _Pragma("unroll") for (int i = 0; i < 4; ++i)
+    {
+        wdx[i] = kDisc.v[lane][i];
+        wone[i] = kDisc.v[lane][4 + i];
+    }
+    const int half = lane & 1;
+    const bool tip = lane >= 62;
+    const int drow = tip ? 15 : lane >> 1, dcol = lane == 62 ? 0 : lane == 63 ? 30 : 1;   // from (-15, -15)
+    const int dy = drow - 15;
+    const uint32_t dhalf = tip ? 0u : 16u * (uint32_t)half;
+    const int wrow = min(lane >> 1, kWinRows - 1);   // window row of this lane
+    struct Pre {
+        v4u d, b;
+        uint32_t sh_d, sh_b;
+    };
+    // Slot records, one per lane: the level's width (0: the keypoint
+    // is closer than 15 pixels to its level's border, or has no level) and the
+    // keypoint's byte offset in the pyramid.
+    int m_w, m_lo, m_hi;
+    {
+        int W = a.w[0], H = a.h[0];
+        int64_t off = a.off[0];
+        _Pragma("unroll") for (int k = 1; k < kLevels; ++k)
+        {
+            W = l == k ? a.w[k] : W;
+            H = l == k ? a.h[k] : H;
+            off = l == k ? a.off[k] : off;
+        }
+        const bool ok = l < kLevels && u >= 15 && v >= 15 && u < W - 15 && v < H - 15;
+        const int64_t at = off + (int64_t)v * W + u;
+        m_w = ok ? W : 0;
+        m_lo = (int)(uint32_t)at;
+        m_hi = (int)(at >> 32);
+    }
+    auto fetch = [&](int s) {
+        Pre p{};
+        const int W = __builtin_amdgcn_readlane(m_w, s);
+        if (W) {
+            const int64_t at = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(m_hi, s) << 32) |
+                                         (uint32_t)__builtin_amdgcn_readlane(m_lo, s));
+            // Every dword read holds a byte of the keypoint's 31 x 31 square, but
+            // for the last three of lane 63's (15, 0), which lie in rows below.
+            const FT_G uint8_t *img = a.pyr + at - 15 * (int64_t)W - 15;
+            const uint32_t si = (uint32_t)reinterpret_cast<uintptr_t>(img) & 3u;
+            const uint32_t od = (uint32_t)(drow * W + dcol) + si;
+            p.sh_d = od & 3u;
+            p.d = *reinterpret_cast<const FT_G v4u_dw *>(img - si + ((od & ~3u) + dhalf));
+            const FT_G uint8_t *B = a.blurred + at - kTurnR * (int64_t)W - kTurnR;
+            const uint32_t sb = (uint32_t)reinterpret_cast<uintptr_t>(B) & 3u;
+            const uint32_t ob = (uint32_t)(wrow * W) + sb;
+            p.sh_b = ob & 3u;
+            p.b = *reinterpret_cast<const FT_G v4u_dw *>(B - sb + ((ob & ~3u) + 16u * (uint32_t)half));
+        }
+        return p;
+    };
+    // e[k]: bytes 4 k .. 4 k + 3 of the lane's 16, from the pixel at shift sh
+    auto realign = [](const v4u &d, uint32_t sh, uint32_t e[4]) {
+        const uint32_t over = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d[0], 0xF5, 0xF, 0xF, false);   // quad_perm 1,1,3,3
+        _Pragma("unroll") for (int k = 0; k < 4; ++k) e[k] = __builtin_amdgcn_alignbyte(k < 3 ? d[k + 1] : over, d[k], sh);
+    };
+    unsigned char *wl = win + 64 * 16 * w;
+    const float mid = (float)(64 * 16 * w + kTurnR * kWinStride + kTurnR);   // the keypoint's byte in `win`
+    if (lane < kDescSlots) list_i[w * kDescSlots + lane] = mine < n ? mine : -1;
+    const int slots = n - wave <= 0 ? 0 : min(kDescSlots, (n - wave + waves - 1) / waves);
+    Pre cur{};
+    if (slots > 0) cur = fetch(0);
+    for (int s = 0; s < slots; ++s) {
+        const int i = s * waves + wave;
+        Pre nxt{};
+        if (s + 1 < slots) nxt = fetch(s + 1);
+        const bool ok = __builtin_amdgcn_readlane(m_w, s) != 0;
         FT_G uint8_t *d = a.desc + 32 * (int64_t)i;
-        int m10 = 0, m01 = 0;
         if (!ok) {   // outside the window the disc and the turned pattern need
             if (lane < 8) reinterpret_cast<FT_G uint32_t *>(d)[lane] = 0u;
-        } else {
-            const int W = a.w[l];
-            const FT_G uint8_t *img = a.pyr + a.off[l] + (int64_t)v * W + u;
-            const FT_G uint8_t *B = a.blurred + a.off[l] + (int64_t)v * W + u;
-            // the 32 x 32 square from (-15, -15): 16 positions per lane, every
-            // load issued before any is used (row and column 16, outside the
-            // disc, load a pixel of row or column 15 and weigh 0)
-            int pix[16];
-            _Pragma("unroll") for (int j = 0; j < 16; ++j)
+            if (lane == 0) list_m10[w * kDescSlots + s] = INT_MIN;
+            cur = nxt;
+            continue;
+        }
+        // moments (exact integers, |m| <= 577,320)
+        int m10 = 0;
+        uint32_t row_sum = 0, e[4];
+        realign(cur.d, cur.sh_d, e);
+        _Pragma("unroll") for (int k = 0; k < 4; ++k)
+        {
+            m10 = __builtin_amdgcn_sdot4((int)(e[k] ^ 0x80808080u), (int)wdx[k], m10, false);
+            row_sum = __builtin_amdgcn_udot4(e[k], wone[k], row_sum, false);
+        }
+        int m01 = dy * (int)row_sum;
+        m10 = wave_sum(m10);
+        m01 = wave_sum(m01);
+        if (lane == 0) {
+            list_m10[w * kDescSlots + s] = m10;
+            list_m01[w * kDescSlots + s] = m01;
+        }
+        // the smoothed window: row wrow at byte 32 wrow of the wave's LDS
+        realign(cur.b, cur.sh_b, e);
+        *reinterpret_cast<v4u *>(wl + 16 * lane) = v4u{e[0], e[1], e[2], e[3]};
+        wave_lds_sync();
+        // per test: the two turned points, then their smoothed pixels.  A
+        // turned coordinate is (x m10 - y m01) / |m| or (x m01 + y m10) / |m|, at
+        // most 13 in size; in binary32 from the direction (m10, m01) / |m| (half a
+        // unit for each square, their sum, both products and the two terms, one
+        // for the reciprocal root) it is off by less than 4.5e-6, so unless it
+        // lies within 1e-5 of a half it rounds to the exact integer, and else is
+        // decided in integers.  m = 0: no turn.
+        const bool turned = (m10 | m01) != 0;
+        const float f10 = (float)m10, f01 = (float)m01;   // exact: |m| < 2^24
+        const float inv_r = turned ? rsqrtf(f10 * f10 + f01 * f01) : 0.0f;
+        const float cs = turned ? f10 * inv_r : 1.0f, sn = f01 * inv_r;
+        int p1[4], p2[4];    // bytes of the test's points in `win`
+        float far[4];        // largest distance of a turned coordinate from its integer
+        auto place = [&](float c, float r) { return (int)fmaf(r, (float)kWinStride, c + mid); };
+        _Pragma("unroll") for (int q = 0; q < 4; ++q)
+        {
+            const float4 t = pattern[64 * q + lane];
+            far[q] = 0.0f;
+            auto turn = [&](float x) {
+                const float r = __builtin_rintf(x);
+                far[q] = fmaxf(far[q], fabsf(x - r));
+                return r;
+            };
+            const float c1 = turn(fmaf(-t.y, sn, t.x * cs)), r1 = turn(fmaf(t.y, cs, t.x * sn));
+            const float c2 = turn(fmaf(-t.w, sn, t.z * cs)), r2 = turn(fmaf(t.w, cs, t.z * sn));
+            p1[q] = place(c1, r1);
+            p2[q] = place(c2, r2);
+        }
+        constexpr float kNear = 0.5f - 1e-5f;
+        if (!(fmaxf(fmaxf(far[0], far[1]), fmaxf(far[2], far[3])) < kNear)) {
+            // (the moments made opaque here, so that nothing of this rare path is
+            // computed outside it)
+            int a10 = turned ? m10 : 1, a01 = m01;
+            asm volatile("" : "+v"(a10), "+v"(a01));
+            const int64_t m2 = (int64_t)a10 * a10 + (int64_t)a01 * a01;
+            _Pragma("unroll 1") for (int q = 0; q < 4; ++q)
             {
-                const int dy = dy0 + 2 * j;
-                pix[j] = img[(dy < 15 ? dy : 15) * W + dxl];
-            }
-            int sx = 0;
-            _Pragma("unroll") for (int j = 0; j < 16; ++j)
-            {
-                const int dy = dy0 + 2 * j;
-                const int w = (dx <= 15 && dx * dx + dy * dy <= 225) ? pix[j] : 0;
-                sx += w;
-                m01 += dy * w;
-            }
-            m10 = wave_sum(dx * sx);
-            m01 = wave_sum(m01);
-            const bool turned = (m10 | m01) != 0;   // the squared radius m10^2 + m01^2 is positive
-            const float f10 = (float)m10, f01 = (float)m01;   // exact: |m| < 2^24
-            const float inv_r = turned ? rsqrtf(f10 * f10 + f01 * f01) : 0.0f;
-            // per test: the two turned points (binary32 estimates, the exact
-            // decision when one lies near a half), then their smoothed pixels
-            uint64_t mask[4];
-            _Pragma("unroll") for (int q = 0; q < 4; ++q)
-            {
-                const int n0 = tx1[q] * m10 - ty1[q] * m01, n1 = tx1[q] * m01 + ty1[q] * m10;
-                const int n2 = tx2[q] * m10 - ty2[q] * m01, n3 = tx2[q] * m01 + ty2[q] * m10;
-                int c1 = tx1[q], r1 = ty1[q], c2 = tx2[q], r2 = ty2[q];
-                if (turned) {
-                    bool near = false;
-                    c1 = turn_fast(n0, inv_r, near);
-                    r1 = turn_fast(n1, inv_r, near);
-                    c2 = turn_fast(n2, inv_r, near);
-                    r2 = turn_fast(n3, inv_r, near);
-                    if (near) {
-                        const int64_t m2 = (int64_t)m10 * m10 + (int64_t)m01 * m01;
-                        c1 = round_ratio_exact(n0, m2);
-                        r1 = round_ratio_exact(n1, m2);
-                        c2 = round_ratio_exact(n2, m2);
-                        r2 = round_ratio_exact(n3, m2);
-                    }
+                const float f = q == 0 ? far[0] : q == 1 ? far[1] : q == 2 ? far[2] : far[3];
+                if (f < kNear) continue;
+                const float4 t = pattern[64 * q + lane];
+                int at[2];
+                _Pragma("unroll 1") for (int k = 0; k < 2; ++k)
+                {
+                    const int x = (int)(k ? t.z : t.x), y = (int)(k ? t.w : t.y);
+                    const int v = place((float)round_ratio_exact(x * a10 - y * a01, m2),
+                                        (float)round_ratio_exact(x * a01 + y * a10, m2));
+                    at[0] = k ? at[0] : v;
+                    at[1] = v;
                 }
-                mask[q] = __ballot(B[r1 * W + c1] < B[r2 * W + c2]);
+                _Pragma("unroll") for (int j = 0; j < 4; ++j)
+                {
+                    p1[j] = q == j ? at[0] : p1[j];
+                    p2[j] = q == j ? at[1] : p2[j];
+                }
             }
-            if (lane < 4) {
-                const uint64_t mq = lane == 0 ? mask[0] : lane == 1 ? mask[1] : lane == 2 ? mask[2] : mask[3];
-                reinterpret_cast<FT_G uint64_t *>(d)[lane] = mq;
-            }
         }
-        if (lane == (slot & 63)) {
-            keep_i = ok ? i : -2 - i;
-            keep_m10 = m10;
-            keep_m01 = m01;
+        uint64_t bits = 0;   // lane q: tests 64 q .. 64 q + 63
+        uint32_t g1[4], g2[4];
+        _Pragma("unroll") for (int q = 0; q < 4; ++q)
+        {
+            g1[q] = win[p1[q]];
+            g2[q] = win[p2[q]];
         }
-        if ((slot & 63) == 63) {
-            if (keep_i >= 0) a.angle[keep_i] = angle_deg(keep_m10, keep_m01);
-            else if (keep_i < -1) a.angle[-2 - keep_i] = -1.0f;
-            keep_i = -1;
+        _Pragma("unroll") for (int q = 0; q < 4; ++q)
+        {
+            const uint64_t m = __ballot(g1[q] < g2[q]);
+            bits = lane == q ? m : bits;
         }
+        wave_lds_sync();   // the window is free for the next keypoint
+        if (lane < 4) reinterpret_cast<FT_G uint64_t *>(d)[lane] = bits;
+        cur = nxt;
     }
-    if (keep_i >= 0) a.angle[keep_i] = angle_deg(keep_m10, keep_m01);
-    else if (keep_i < -1) a.angle[-2 - keep_i] = -1.0f;
+    // the workgroup's angles, one per lane of one wave
+    __syncthreads();
+    if (w == 0) {
+        const int i = list_i[lane], m10 = list_m10[lane], m01 = list_m01[lane];
+        if (i >= 0) a.angle[i] = m10 == INT_MIN ? -1.0f : angle_deg(m10, m01);
+    }
 }
 
 }  // namespace
@@ -523,9 +656,12 @@ hipError_t launch_orb_detect(const OrbDetectArgs &a, hipStream_t s)
 hipError_t launch_orb_describe(const OrbDescribeArgs &a, hipStream_t s)
 {
     if (a.n_max <= 0) return hipSuccess;
-    const int per_block = kThreads / 64;
-    int blocks = (a.n_max + per_block - 1) / per_block;
-    if (blocks > 2048) blocks = 2048;
+    // One wave per keypoint up to four waves per SIMD of the chip's 256 CUs, then
+    // up to kDescSlots keypoints per wave (so a wave's set-up and its share of
+    // the binary64 angles are paid less often), then more workgroups.
+    const int most = kDescWaves * kDescSlots;
+    int blocks = (a.n_max + kDescWaves - 1) / kDescWaves;
+    blocks = std::max(std::min(blocks, 1024), (a.n_max - 1) / most + 1);
     hipLaunchKernelGGL(k_orb_describe, dim3(blocks), dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }
