@@ -649,8 +649,16 @@ ft_status enter(ft_context *ctx)
     return FT_OK;
 }
 
-ft_status launch_one(ft_context *ctx, const DevJob &J, hipStream_t s, bool stereo, bool search)
+// Workgroups per row or cell sort: split while the chip's 256 CUs have room (one
+// view of 3000 keypoints, 20,000 map points: 26.3 us per search call with one
+// workgroup, 25.1 with two, 23.1 with four, 22.9 with eight); a batch that fills
+// them has one each, since every part reads all keypoints (64 mixed frames, 160
+// sorts: 176 us per batch with one, 179 with two, 185 with four).
+int setup_split(int sorts) { return 4 * sorts <= 256 ? 4 : 2 * sorts <= 256 ? 2 : 1; }
+
+ft_status launch_one(ft_context *ctx, DevJob &J, hipStream_t s, bool stereo, bool search)
 {
+    J.setup_split = setup_split((stereo ? 1 : 0) + (search ? J.n_views : 0));
     int32_t tot[PH_COUNT];
     job_tiles(J, ctx->shapes, stereo, search, tot);
     TileMap none{0, nullptr};
@@ -665,7 +673,12 @@ ft_status build_batch(ft_context *ctx, Lane &lane, const ft_frame_job *jobs, int
     DevJob *table = reinterpret_cast<DevJob *>(lane.h_table + ctx->layout.jobs_off);
     int64_t kp_total = 0, map_total = 0;
     int images = 0;   // images whose pyramids the batch builds
-    for (int f = 0; f < n; ++f) images += jobs[f].kind == FT_JOB_PINHOLE && jobs[f].build_pyramids ? 2 : 0;
+    int sorts = 0;    // row sorts, overlap lists and cell sorts of the setup phase
+    for (int f = 0; f < n; ++f) {
+        images += jobs[f].kind == FT_JOB_PINHOLE && jobs[f].build_pyramids ? 2 : 0;
+        sorts += (jobs[f].kind != FT_JOB_SEARCH) + (jobs[f].n_views > 0 && jobs[f].n_views <= 2 ? jobs[f].n_views : 0);
+    }
+    const int split = setup_split(sorts);
     for (int f = 0; f < n; ++f) {
         const ft_frame_job &jb = jobs[f];
         const bool stereo = jb.kind == FT_JOB_PINHOLE || jb.kind == FT_JOB_FISHEYE;
@@ -673,6 +686,7 @@ ft_status build_batch(ft_context *ctx, Lane &lane, const ft_frame_job *jobs, int
         map_total += jb.n_views > 0 ? (int64_t)jb.map.n : 0;
         DevJob &J = table[f];
         J = DevJob{};
+        J.setup_split = split;
         const Slot &slot = lane.slots[f];
         if (jb.kind == FT_JOB_PINHOLE) {
             if ((st = build_pinhole(ctx, J, &jb.left, &jb.right, &jb.pyr_left, &jb.pyr_right, &jb.scales,

@@ -113,6 +113,7 @@ struct DevJob {
     int32_t flags;
     int32_t nM;
     int32_t n_views;
+    int32_t setup_split;             // workgroups of a row or cell sort (1, 2, 4 or 8)
     DevKps L, R;
     float sf[kLevels], inv_sf[kLevels], sigma2[kLevels];
     // pinhole stereo

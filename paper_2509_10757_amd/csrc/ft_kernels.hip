@@ -162,36 +162,59 @@ __device__ __forceinline__ int wave_inclusive_max(int v) { return wave_inclusive
 // Value of lane 63 (the total of an inclusive scan), wave-uniform.
 __device__ __forceinline__ int wave_last(int v) { return __builtin_amdgcn_readlane(v, 63); }
 
-// Workgroup-wide exclusive scan of a[0..n) in LDS; returns the total.  Each
-// thread owns a contiguous run of a[], the runs' sums are scanned inside each
-// wave with lane shuffles, and the waves' totals (tmp[0..NT/64)) are combined
-// after one barrier.
-template <int NT>
-__device__ __forceinline__ int wg_exclusive_scan(int *a, int n, int *tmp)
+// Workgroup-wide exclusive scan, from `base` up, of a[0..n) in LDS (16-byte
+// aligned, room for n rounded up to 4, zero past n); returns base + the total.
+// Each thread owns a contiguous run of whole 16-byte groups (one LDS read per
+// four entries, no bank conflicts), the runs' sums are scanned inside each wave,
+// and the waves' totals (tmp[0..NT/64)) are combined after one barrier.  `emit`
+// receives every group (index, its four prefixes) as it is written back.  `add`
+// is summed over the threads into every prefix (records before the first bin).
+template <int NT, class Emit>
+__device__ __forceinline__ int wg_exclusive_scan(int *a, int n, int *tmp, int add, Emit emit)
 {
     constexpr int NW = NT / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = (n + NT - 1) / NT;
+    const int per = ((n + 4 * NT - 1) / (4 * NT)) * 4;
     const int beg = min(tid * per, n), end = min(beg + per, n);
     int s = 0;
-    for (int i = beg; i < end; ++i) s += a[i];
+    for (int i = beg; i < end; i += 4) {
+        const v4i v = *reinterpret_cast<const v4i *>(a + i);
+        s += (v[0] + v[1]) + (v[2] + v[3]);
+    }
     const int inc = wave_inclusive_scan(s);
-    if (lane == 63) tmp[wave] = inc;
+    const int before = wave_last(wave_inclusive_scan(add));
+    if (lane == 63) {
+        tmp[wave] = inc;
+        tmp[NW + wave] = before;
+    }
     __syncthreads();
     int run = inc - s, total = 0;
     _Pragma("unroll") for (int w = 0; w < NW; ++w)
     {
-        const int t = tmp[w];
-        run += w < wave ? t : 0;
-        total += t;
+        const int t = tmp[w], u = tmp[NW + w];
+        run += (w < wave ? t : 0) + u;
+        total += t + u;
     }
-    for (int i = beg; i < end; ++i) {
-        const int v = a[i];
-        a[i] = run;
-        run += v;
+    for (int i = beg; i < end; i += 4) {
+        const v4i v = *reinterpret_cast<const v4i *>(a + i);
+        v4i e;
+        _Pragma("unroll") for (int k = 0; k < 4; ++k)
+        {
+            e[k] = run;
+            run += v[k];
+        }
+        *reinterpret_cast<v4i *>(a + i) = e;
+        emit(i, e);
     }
     __syncthreads();
     return total;
+}
+
+// Zeroes a[0..n rounded up to 4) (LDS, 16-byte aligned).
+template <int NT>
+__device__ __forceinline__ void lds_zero(int *a, int n)
+{
+    for (int i = 4 * (int)threadIdx.x; i < n; i += 4 * NT) *reinterpret_cast<v4i *>(a + i) = v4i{0, 0, 0, 0};
 }
 
 __device__ __forceinline__ int cell_coord(float v, float lo, float inv, int n)
@@ -520,16 +543,21 @@ __device__ __forceinline__ uint32_t band_rows(const DevJob &J, float y, int oct)
     return (uint32_t)lo | ((uint32_t)hi << 16);
 }
 
+// Levels [part * kLevels / parts, ..) of the row sort, one workgroup each
+// (`parts` = 1: the one bin of every level).  A workgroup reads every right
+// keypoint and keeps its own levels'; the records of lower levels are counted
+// on the way, so the parts need nothing from each other.
 template <int NT>
-__device__ __forceinline__ void ph_rowsort(const DevJob &J, int *cnt, int *tmp)
+__device__ __forceinline__ void ph_rowsort(const DevJob &J, int part, int parts, int *cnt, int *tmp)
 {
     const int tid = threadIdx.x;
-    const int rows = J.rows, nR = J.R.n, nb = J.n_lb * rows;
+    const int rows = J.rows, nR = J.R.n;
+    const int b0 = part * J.n_lb / parts, b1 = (part + 1) * J.n_lb / parts, nb = (b1 - b0) * rows;
     const bool per_level = J.n_lb > 1;
-    for (int r = tid; r < nb; r += NT) cnt[r] = 0;
-    for (int j = tid; j < nR; j += NT) J.claimR[j] = 0xFFFFFFFFu;
-    for (int i = tid; i < J.L.n; i += NT) J.flag[i] = 0;   // the refinement flags matches only
-    if (tid == 0) J.counts[2] = 0;                          // length of the match list
+    lds_zero<NT>(cnt, nb);
+    for (int j = part * NT + tid; j < nR; j += parts * NT) J.claimR[j] = 0xFFFFFFFFu;
+    for (int i = part * NT + tid; i < J.L.n; i += parts * NT) J.flag[i] = 0;   // the refinement flags matches only
+    if (part == 0 && tid == 0) J.counts[2] = 0;                                // length of the match list
     __syncthreads();
     // A chunk of kSortUnroll right keypoints per thread; the first chunk stays
     // in registers from the counting pass to the scatter.
@@ -542,17 +570,29 @@ __device__ __forceinline__ void ph_rowsort(const DevJob &J, int *cnt, int *tmp)
             oc[e] = J.R.oct[j];
         }
     };
-    auto bin_of = [&](float y, int oc) { return (per_level ? lvl(oc) * rows : 0) + row_bin(y, rows); };
+    // bin of this part, or -1 (a lower level: -2)
+    auto bin_of = [&](float y, int oc) {
+        const int lb = per_level ? lvl(oc) : 0;
+        return lb < b0 ? -2 : lb >= b1 ? -1 : (lb - b0) * rows + row_bin(y, rows);
+    };
+    int lower = 0;
     auto count = [&](int j0, const float *y, const int *oc) {
         _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
-            if (j0 + e * NT < nR) atomicAdd(&cnt[bin_of(y[e], oc[e])], 1);
+        {
+            if (j0 + e * NT < nR) {
+                const int b = bin_of(y[e], oc[e]);
+                if (b >= 0) atomicAdd(&cnt[b], 1);
+                lower += b == -2 ? 1 : 0;
+            }
+        }
     };
     auto scatter = [&](int j0, const float *x, const float *y, const int *oc) {
         _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
         {
             const int j = j0 + e * NT;
-            if (j < nR) {
-                const int pos = atomicAdd(&cnt[bin_of(y[e], oc[e])], 1);
+            const int b = j < nR ? bin_of(y[e], oc[e]) : -1;
+            if (b >= 0) {
+                const int pos = atomicAdd(&cnt[b], 1);
                 RowRec rec;
                 rec.x = x[e];
                 rec.band = band_rows(J, y[e], oc[e]);
@@ -575,12 +615,12 @@ __device__ __forceinline__ void ph_rowsort(const DevJob &J, int *cnt, int *tmp)
         count(j0, y, oc);
     }
     __syncthreads();
-    const int total = wg_exclusive_scan<NT>(cnt, nb, tmp);
+    const int total = wg_exclusive_scan<NT>(cnt, nb, tmp, lower, [](int, v4i) {});
     // row_start[lb][r] = first record of (lb, r); row_start[lb][rows] = end of level bin lb
-    for (int e = tid; e < J.n_lb * (rows + 1); e += NT) {
+    for (int e = tid; e < (b1 - b0) * (rows + 1); e += NT) {
         const int lb = e / (rows + 1), r = e - lb * (rows + 1);
         const int bin = lb * rows + r;
-        J.row_start[e] = bin < nb ? cnt[bin] : total;
+        J.row_start[b0 * (rows + 1) + e] = bin < nb ? cnt[bin] : total;
     }
     __syncthreads();
     if (tid < nR) scatter(tid, x0, y0, oc0);
@@ -593,45 +633,77 @@ __device__ __forceinline__ void ph_rowsort(const DevJob &J, int *cnt, int *tmp)
 }
 
 // ------------------------------------------- setup: overlap lists (fisheye)
-template <int NT>
-__device__ __forceinline__ int compact_range(const float *x, int n, float a, float b, int32_t *out, int *wsum)
+// Indices i < n with a <= x[i] <= b, in order, into out[]; with `desc`, their
+// descriptors in the same order into tdesc.  U keypoints per thread
+// and round, their loads together; a round's counts per (keypoint, wave) are
+// scanned by every wave after one barrier.
+template <int NT, int U>
+__device__ __forceinline__ int compact_range(const FT_G float *x, int n, float a, float b, FT_G int32_t *out,
+                                             const FT_G uint8_t *desc, FT_G uint8_t *tdesc, int *wcnt)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NW = NT / 64;
+    static_assert(U * NW <= 64, "one lane per (keypoint, wave) count");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const FT_G v4u *src = reinterpret_cast<const FT_G v4u *>(desc);
+    FT_G v4u *dst = reinterpret_cast<FT_G v4u *>(tdesc);
     int base = 0;
-    for (int s = 0; s < n; s += NT) {
-        const int i = s + tid;
-        const bool p = i < n && x[i] >= a && x[i] <= b;
-        const unsigned long long m = __ballot(p);
-        const int rank = __popcll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) wsum[wave] = __popcll(m);
+    for (int s = 0; s < n; s += U * NT) {
+        bool p[U];
+        int rank[U];
+        v4u d[U][2];
+        _Pragma("unroll") for (int e = 0; e < U; ++e)
+        {
+            const int i = s + e * NT + tid;
+            const float v = x[min(i, n - 1)];
+            p[e] = i < n && v >= a && v <= b;
+            if (desc && p[e]) {
+                d[e][0] = src[2 * (size_t)i];
+                d[e][1] = src[2 * (size_t)i + 1];
+            }
+        }
+        _Pragma("unroll") for (int e = 0; e < U; ++e)
+        {
+            const unsigned long long m = __ballot(p[e]);
+            rank[e] = __popcll(m & ((1ull << lane) - 1ull));
+            if (lane == 0) wcnt[e * NW + wave] = __popcll(m);
+        }
         __syncthreads();
-        int off = base;
-        for (int w = 0; w < wave; ++w) off += wsum[w];
-        if (p) out[off + rank] = i;
-        int tot = 0;
-        for (int w = 0; w < NT / 64; ++w) tot += wsum[w];
-        __syncthreads();
-        base += tot;
+        const int inc = wave_inclusive_scan(lane < U * NW ? wcnt[lane] : 0);
+        _Pragma("unroll") for (int e = 0; e < U; ++e)
+        {
+            const int j = e * NW + wave;
+            const int pos = base + rank[e] + (j ? __builtin_amdgcn_readlane(inc, (j - 1) & 63) : 0);
+            if (p[e]) {
+                out[pos] = s + e * NT + tid;
+                if (desc) {
+                    dst[2 * (size_t)pos] = d[e][0];
+                    dst[2 * (size_t)pos + 1] = d[e][1];
+                }
+            }
+        }
+        base += wave_last(inc);
+        __syncthreads();   // the counts are free for the next round
     }
     return base;
 }
 
+// Part 0: the query list; part 1: the target list and the targets' descriptors
+// in its order.
 template <int NT>
-__device__ __forceinline__ void ph_overlap(const DevJob &J, int *wsum)
+__device__ __forceinline__ void ph_overlap(const DevJob &J, int part, int *wcnt)
 {
     const int tid = threadIdx.x;
-    for (int j = tid; j < J.R.n; j += NT) J.claimR[j] = 0xFFFFFFFFu;
-    for (int i = tid; i < J.L.n; i += NT) J.flag[i] = 0;
-    const int nQ = compact_range<NT>(J.L.x, J.L.n, J.ovl[0], J.ovl[1], J.qlist, wsum);
-    const int nT = compact_range<NT>(J.R.x, J.R.n, J.ovr[0], J.ovr[1], J.tlist, wsum);
-    // targets' descriptors in overlap order: one 16-byte half per thread step
-    const uint4 *src = reinterpret_cast<const uint4 *>(J.R.desc);
-    uint4 *dst = reinterpret_cast<uint4 *>(J.tdesc);
-    for (int h = tid; h < 2 * nT; h += NT) dst[h] = src[2 * J.tlist[h >> 1] + (h & 1)];
-    if (tid == 0) {
-        J.counts[0] = nQ;
-        J.counts[1] = nT;
-        *J.o_nmatch = 0;
+    if (part == 0) {
+        for (int i = tid; i < J.L.n; i += NT) J.flag[i] = 0;
+        const int nQ = compact_range<NT, kSortUnroll>(J.L.x, J.L.n, J.ovl[0], J.ovl[1], J.qlist, nullptr, nullptr, wcnt);
+        if (tid == 0) {
+            J.counts[0] = nQ;
+            *J.o_nmatch = 0;
+        }
+    } else {
+        for (int j = tid; j < J.R.n; j += NT) J.claimR[j] = 0xFFFFFFFFu;
+        const int nT = compact_range<NT, 2>(J.R.x, J.R.n, J.ovr[0], J.ovr[1], J.tlist, J.R.desc, J.tdesc, wcnt);
+        if (tid == 0) J.counts[1] = nT;
     }
 }
 
@@ -652,23 +724,28 @@ __device__ __forceinline__ void cell_bins(const DevView &V, int o, int lv_lo, in
 
 // Counting sort of the view's keypoints by (level bin, row, column) into
 // 16-byte records; a keypoint is copied into every bin that holds its octave.
+// One workgroup per part: level bins [part * n_pb / parts, ..), each reading
+// every keypoint and counting the copies that go to lower bins, so the parts
+// need nothing from each other.
 template <int NT>
-__device__ __forceinline__ void ph_cellsort(const DevView &V, const DevKps &K, int lv_lo, int lv_hi, int *cnt,
-                                            int *tmp)
+__device__ __forceinline__ void ph_cellsort(const DevView &V, const DevKps &K, int lv_lo, int lv_hi, int part, int parts,
+                                            int *cnt, int *tmp)
 {
     const int tid = threadIdx.x;
     const int cells = V.cols * V.rows;
-    const int nb = V.n_pb * cells;
-    for (int c = tid; c < nb; c += NT) cnt[c] = 0;
-    for (int k = tid; k < K.n; k += NT) V.claim[k] = 0xFFFFFFFFu;
-    for (int b = tid; b < kRotBinsMax; b += NT) V.hist[b] = 0;
-    if (tid == 0) *V.n_matches = 0;
+    const int b0 = part * V.n_pb / parts, b1 = (part + 1) * V.n_pb / parts, nb = (b1 - b0) * cells;
+    lds_zero<NT>(cnt, nb);
+    for (int k = part * NT + tid; k < K.n; k += parts * NT) V.claim[k] = 0xFFFFFFFFu;
+    if (part == 0) {
+        for (int b = tid; b < kRotBinsMax; b += NT) V.hist[b] = 0;
+        if (tid == 0) *V.n_matches = 0;
+    }
     __syncthreads();
-    // A chunk of kSortUnroll keypoints per thread: the cell, position and
-    // record meta of each (load), its counts (count) and its records (scatter).
-    // The first chunk stays in registers from the counting pass to the scatter,
-    // so a view of up to kSortUnroll * NT keypoints is read once.
-    auto load = [&](int k0, int *cell, float *x, float *y, uint32_t *meta) {
+    // A chunk of kSortUnroll keypoints per thread: the position and record meta
+    // of each (load), its counts (count) and its records (scatter).  The first
+    // chunk stays in registers from the counting pass to the scatter, so a view
+    // of up to kSortUnroll * NT keypoints is read once per part.
+    auto load = [&](int k0, float *x, float *y, uint32_t *meta) {
         _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
         {
             const int k = min(k0 + e * NT, K.n - 1);
@@ -677,24 +754,25 @@ __device__ __forceinline__ void ph_cellsort(const DevView &V, const DevKps &K, i
             const uint32_t pre = (V.preassigned && V.preassigned[k]) ? 1u : 0u;
             meta[e] = (uint32_t)K.oct[k] | (pre << 8) | ((uint32_t)k << 16);
         }
-        _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
-        {
-            const int cx = cell_coord(x[e], V.min_x, V.inv_cw, V.cols);
-            const int cy = cell_coord(y[e], V.min_y, V.inv_ch, V.rows);
-            cell[e] = cy * V.cols + cx;
-        }
     };
-    auto count = [&](int k0, const int *cell, const uint32_t *meta) {
+    auto cell_of = [&](float x, float y) {
+        return cell_coord(y, V.min_y, V.inv_ch, V.rows) * V.cols + cell_coord(x, V.min_x, V.inv_cw, V.cols);
+    };
+    int lower = 0;
+    auto count = [&](int k0, const float *x, const float *y, const uint32_t *meta) {
         _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
         {
             if (k0 + e * NT < K.n) {
-                int p0, p1;
-                cell_bins(V, (int)(meta[e] & 0xFFu), lv_lo, lv_hi, p0, p1);
-                for (int p = p0; p <= p1; ++p) atomicAdd(&cnt[p * cells + cell[e]], 1);
+                int q0, q1;
+                cell_bins(V, (int)(meta[e] & 0xFFu), lv_lo, lv_hi, q0, q1);
+                lower += max(min(q1 + 1, b0) - q0, 0);
+                const int p0 = max(q0, b0), p1 = min(q1, b1 - 1);
+                int c = (p0 - b0) * cells + cell_of(x[e], y[e]);
+                for (int p = p0; p <= p1; ++p, c += cells) atomicAdd(&cnt[c], 1);
             }
         }
     };
-    auto scatter = [&](int k0, const int *cell, const float *x, const float *y, const uint32_t *meta) {
+    auto scatter = [&](int k0, const float *x, const float *y, const uint32_t *meta) {
         _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
         {
             if (k0 + e * NT < K.n) {
@@ -703,38 +781,42 @@ __device__ __forceinline__ void ph_cellsort(const DevView &V, const DevKps &K, i
                 rec.y = y[e];
                 rec.meta = meta[e];
                 rec.pad = 0;
-                int p0, p1;
-                cell_bins(V, (int)(meta[e] & 0xFFu), lv_lo, lv_hi, p0, p1);
-                for (int p = p0; p <= p1; ++p) V.crec[atomicAdd(&cnt[p * cells + cell[e]], 1)] = rec;
+                int q0, q1;
+                cell_bins(V, (int)(meta[e] & 0xFFu), lv_lo, lv_hi, q0, q1);
+                const int p0 = max(q0, b0), p1 = min(q1, b1 - 1);
+                int c = (p0 - b0) * cells + cell_of(x[e], y[e]);
+                for (int p = p0; p <= p1; ++p, c += cells) V.crec[atomicAdd(&cnt[c], 1)] = rec;
             }
         }
     };
-    int cell0[kSortUnroll];
     float x0[kSortUnroll], y0[kSortUnroll];
     uint32_t meta0[kSortUnroll];
     if (tid < K.n) {
-        load(tid, cell0, x0, y0, meta0);
-        count(tid, cell0, meta0);
+        load(tid, x0, y0, meta0);
+        count(tid, x0, y0, meta0);
     }
     for (int k0 = tid + kSortUnroll * NT; k0 < K.n; k0 += kSortUnroll * NT) {
-        int cell[kSortUnroll];
         float x[kSortUnroll], y[kSortUnroll];
         uint32_t meta[kSortUnroll];
-        load(k0, cell, x, y, meta);
-        count(k0, cell, meta);
+        load(k0, x, y, meta);
+        count(k0, x, y, meta);
     }
     __syncthreads();
-    const int total = wg_exclusive_scan<NT>(cnt, nb, tmp);
-    for (int c = tid; c < nb; c += NT) V.cell_off[c] = cnt[c];
-    if (tid == 0) V.cell_off[nb] = total;
-    __syncthreads();
-    if (tid < K.n) scatter(tid, cell0, x0, y0, meta0);
+    FT_G int32_t *off = V.cell_off + b0 * cells;
+    const int total = wg_exclusive_scan<NT>(cnt, nb, tmp, lower, [&](int i, v4i e) {
+        if (i + 4 <= nb) {
+            *reinterpret_cast<FT_G v4u_dw *>(off + i) = __builtin_bit_cast(v4u, e);
+        } else {
+            _Pragma("unroll") for (int k = 0; k < 3; ++k) if (i + k < nb) off[i + k] = e[k];
+        }
+    });
+    if (part == parts - 1 && tid == 0) off[nb] = total;
+    if (tid < K.n) scatter(tid, x0, y0, meta0);
     for (int k0 = tid + kSortUnroll * NT; k0 < K.n; k0 += kSortUnroll * NT) {
-        int cell[kSortUnroll];
         float x[kSortUnroll], y[kSortUnroll];
         uint32_t meta[kSortUnroll];
-        load(k0, cell, x, y, meta);
-        scatter(k0, cell, x, y, meta);
+        load(k0, x, y, meta);
+        scatter(k0, x, y, meta);
     }
 }
 
@@ -1520,38 +1602,51 @@ __device__ __forceinline__ void ph_tri(const DevJob &J, int tile)
 
 // ---------------------- stereo_c (pinhole): conflicts + median + outputs
 // The median is the value at rank n/2 of the survivors' 16-bit SADs, found by
-// a two-pass 8-bit radix select with a parallel prefix over the 256 bins.
-template <int NT>
-__device__ __forceinline__ int select_bin(int *hist, int *tmp, int target, int *out_rank, int *found)
+// a two-pass 8-bit radix select.  Every wave reads the 256 counts (four bins per
+// lane) and selects by itself, so a pass costs one barrier: what bounds the
+// phase is its chain of barriers and loads in one workgroup.
+
+// Bin of hist[256] that holds rank `target` (the total's half when negative),
+// the rank inside it, and the total; wave-uniform.
+__device__ __forceinline__ int select_bin(const int *hist, int target, int &rank, int &total)
 {
-    const int tid = threadIdx.x;
-    const int h = tid < 256 ? hist[tid] : 0;
-    wg_exclusive_scan<NT>(hist, 256, tmp);   // hist now holds exclusive prefixes
-    if (tid < 256 && h > 0 && hist[tid] <= target && target < hist[tid] + h) {
-        found[0] = tid;
-        found[1] = target - hist[tid];
+    const int lane = threadIdx.x & 63;
+    const v4i h = *reinterpret_cast<const v4i *>(hist + 4 * lane);
+    const int s = (h[0] + h[1]) + (h[2] + h[3]);
+    const int inc = wave_inclusive_scan(s);
+    total = wave_last(inc);
+    const int t = target < 0 ? total / 2 : target;
+    int run = inc - s, bin = 4 * lane, left = 0;
+    const bool here = run <= t && t < inc;
+    _Pragma("unroll") for (int k = 0; k < 4; ++k)
+    {
+        const bool in = run <= t && t < run + h[k];
+        bin = in ? 4 * lane + k : bin;
+        left = in ? t - run : left;
+        run += h[k];
     }
-    __syncthreads();
-    *out_rank = found[1];
-    const int b = found[0];
-    __syncthreads();
-    return b;
+    const int at = max(__ffsll((long long)__ballot(here)) - 1, 0);   // (no lane when the total is 0)
+    rank = __builtin_amdgcn_readlane(left, at);
+    return __builtin_amdgcn_readlane(bin, at);
 }
 
 __device__ __forceinline__ bool bit(const uint32_t *b, int i) { return (b[i >> 5] >> (i & 31)) & 1u; }
 
+constexpr int kMedianLds = (256 + 256 + 16) * 4 + (kMaxKp + 32) / 32 * 4;   // counts, kept per wave, survivor bits
+
 template <int NT>
-__device__ __forceinline__ void ph_median(const DevJob &J, int *hist, int *tmp, uint32_t *surv, int *sh)
+__device__ __forceinline__ void ph_median(const DevJob &J, unsigned char *smem)
 {
+    int *hist = reinterpret_cast<int *>(smem), *hist2 = hist + 256, *wkept = hist + 512;
+    uint32_t *surv = reinterpret_cast<uint32_t *>(hist + 528);
     const int tid = threadIdx.x, nL = J.L.n;
     // Up to kSortUnroll * NT keypoints, every field a thread needs stays in
     // its registers from the first pass to the outputs; larger frames re-read.
     const bool held = nL <= kSortUnroll * NT;
-    if (tid < 256) hist[tid] = 0;
-    if (tid == 0) sh[0] = 0;
-    for (int w = tid; w < (nL + 31) / 32; w += NT) surv[w] = 0;
+    for (int b = tid; b < 512; b += NT) hist[b] = 0;
+    if (!held)
+        for (int w = tid; w < (nL + 31) / 32; w += NT) surv[w] = 0;
     __syncthreads();
-    int my_n = 0;
     int bj[kSortUnroll], bh[kSortUnroll], sd[kSortUnroll];
     float ur[kSortUnroll], dp[kSortUnroll];
     bool sv[kSortUnroll] = {};
@@ -1575,35 +1670,26 @@ __device__ __forceinline__ void ph_median(const DevJob &J, int *hist, int *tmp, 
             const int i = i0 + e * NT;
             sv[e] = i < nL && fl[e] && cl[e] == (((uint32_t)bh[e] << 23) | (uint32_t)i);
             if (sv[e]) {
-                atomicOr(&surv[i >> 5], 1u << (i & 31));
-                ++my_n;
+                if (!held) atomicOr(&surv[i >> 5], 1u << (i & 31));
                 atomicAdd(&hist[(sd[e] >> 8) & 0xFF], 1);
             }
         }
     }
-    atomicAdd(&sh[0], my_n);
     __syncthreads();
-    const int n = sh[0];
-    int m = 0;
-    if (n > 0) {
-        int rank;
-        const int hb = select_bin<NT>(hist, tmp, n / 2, &rank, sh + 2);
-        if (tid < 256) hist[tid] = 0;
-        __syncthreads();
+    int rank, n, m = 0;
+    const int hb = select_bin(hist, -1, rank, n);
+    if (n > 0) {   // (uniform)
         if (held) {
             _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
-                if (tid + e * NT < nL && sv[e] && ((sd[e] >> 8) & 0xFF) == hb) atomicAdd(&hist[sd[e] & 0xFF], 1);
+                if (tid + e * NT < nL && sv[e] && ((sd[e] >> 8) & 0xFF) == hb) atomicAdd(&hist2[sd[e] & 0xFF], 1);
         } else {
             for (int i = tid; i < nL; i += NT)
-                if (bit(surv, i) && ((J.sad[i] >> 8) & 0xFF) == hb) atomicAdd(&hist[J.sad[i] & 0xFF], 1);
+                if (bit(surv, i) && ((J.sad[i] >> 8) & 0xFF) == hb) atomicAdd(&hist2[J.sad[i] & 0xFF], 1);
         }
         __syncthreads();
-        int rank2;
-        const int lb = select_bin<NT>(hist, tmp, rank, &rank2, sh + 2);
-        m = (hb << 8) | lb;
+        int rank2, n2;
+        m = (hb << 8) | select_bin(hist2, rank, rank2, n2);
     }
-    if (tid == 0) sh[1] = 0;
-    __syncthreads();
     int kept = 0;
     for (int i0 = tid; i0 < nL; i0 += kSortUnroll * NT) {
         if (!held) {
@@ -1631,9 +1717,13 @@ __device__ __forceinline__ void ph_median(const DevJob &J, int *hist, int *tmp, 
             kept += keep ? 1 : 0;
         }
     }
-    atomicAdd(&sh[1], kept);
+    kept = wave_last(wave_inclusive_scan(kept));
+    if ((tid & 63) == 0) wkept[tid >> 6] = kept;
     __syncthreads();
-    if (tid == 0) *J.o_nmatch = sh[1];
+    if (tid < 64) {
+        const int all = wave_last(wave_inclusive_scan(tid < NT / 64 ? wkept[tid] : 0));
+        if (tid == 0) *J.o_nmatch = all;
+    }
 }
 
 // ---------------------- stereo_c (fisheye): conflicts + outputs
@@ -2292,6 +2382,15 @@ __host__ __device__ inline int final_tiles_view(const DevJob &J, int v)
     return div_up(J.nM > nK ? J.nM : nK, kWG);
 }
 
+// Workgroups of the setup phase: J.setup_split for the row sort by level and
+// each view's cell sort by level bin (indexes with one bin: one workgroup), two
+// for the overlap lists.
+__host__ __device__ inline int setup_parts_stereo(const DevJob &J)
+{
+    return J.flags & JOB_STEREO_FISHEYE ? 2 : J.n_lb > 1 ? J.setup_split : 1;
+}
+__host__ __device__ inline int setup_parts_view(const DevJob &J, int v) { return J.view[v].n_pb > 1 ? J.setup_split : 1; }
+
 void job_tiles(const DevJob &J, const Shapes &s, bool do_stereo, bool do_search, int32_t out[PH_COUNT])
 {
     for (int p = 0; p < PH_COUNT; ++p) out[p] = 0;
@@ -2300,7 +2399,8 @@ void job_tiles(const DevJob &J, const Shapes &s, bool do_stereo, bool do_search,
     const bool pin = do_stereo && (J.flags & JOB_STEREO_PINHOLE);
     const bool fish = do_stereo && (J.flags & JOB_STEREO_FISHEYE);
     const int nv = do_search ? J.n_views : 0;
-    out[PH_SETUP] = (pin || fish ? 1 : 0) + nv;
+    out[PH_SETUP] = pin || fish ? setup_parts_stereo(J) : 0;
+    for (int v = 0; v < nv; ++v) out[PH_SETUP] += setup_parts_view(J, v);
     if (pin) {
         out[PH_STEREO_A] = div_up(nL, kWG / s.best_lanes);
         out[PH_REFINE] = div_up(nL, refine_quarter(J) ? kRefineQPerWG : kRefinePerWG);
@@ -2366,15 +2466,19 @@ __device__ __forceinline__ void task_setup(const DevJob &J, int tile, unsigned c
 {
     int *lds = reinterpret_cast<int *>(smem);
     int *tmp = lds + kMaxCells + 8;
-    const bool stereo = J.flags & (JOB_STEREO_PINHOLE | JOB_STEREO_FISHEYE);
-    if (stereo && tile == 0) {
-        if (J.flags & JOB_STEREO_PINHOLE) ph_rowsort<NT>(J, lds, tmp);
-        else ph_overlap<NT>(J, tmp);
-        return;
+    if (J.flags & (JOB_STEREO_PINHOLE | JOB_STEREO_FISHEYE)) {
+        const int n = setup_parts_stereo(J);
+        if (tile < n) {
+            if (J.flags & JOB_STEREO_PINHOLE) ph_rowsort<NT>(J, tile, n, lds, tmp);
+            else ph_overlap<NT>(J, tile, tmp);
+            return;
+        }
+        tile -= n;
     }
-    const int v = tile - (stereo ? 1 : 0);
+    const int n0 = setup_parts_view(J, 0);
+    const int v = tile < n0 ? 0 : 1;
     const DevView &V = J.view[v];
-    ph_cellsort<NT>(V, V.side ? J.R : J.L, J.lv_lo, J.lv_hi, lds, tmp);
+    ph_cellsort<NT>(V, V.side ? J.R : J.L, J.lv_lo, J.lv_hi, tile - (v ? n0 : 0), setup_parts_view(J, v), lds, tmp);
 }
 
 template <int G>
@@ -2389,11 +2493,7 @@ __device__ __forceinline__ void task_stereo_a(const DevJob &J, int tile, unsigne
 template <int NT>
 __device__ __forceinline__ void task_stereo_c(const DevJob &J, int tile, unsigned char *smem)
 {
-    int *hist = reinterpret_cast<int *>(smem);
-    int *tmp = hist + 256;
-    int *sh = tmp + NT;
-    uint32_t *surv = reinterpret_cast<uint32_t *>(sh + 8);
-    if (J.flags & JOB_STEREO_PINHOLE) ph_median<NT>(J, hist, tmp, surv, sh);
+    if (J.flags & JOB_STEREO_PINHOLE) ph_median<NT>(J, smem);
     else ph_fish_final<NT>(J, tile);
 }
 
@@ -2419,7 +2519,7 @@ static_assert(256 * 8 + 4 * kKnnQueriesPerWG * 2 * 4 <= kTaskLds, "stereo_a LDS"
 static_assert(kRefinePerWG * kRefineLds <= kTaskLds, "refine LDS");
 static_assert(kRefineQPerWG * kRefineQLds <= kTaskLds, "refine LDS (quarter waves)");
 static_assert(kDealLdsPerWave <= kTaskLds, "record-dealt search LDS");
-static_assert((256 + kWG + 8) * 4 + (kMaxKp + 32) / 32 * 4 <= kTaskLds, "median LDS");
+static_assert(kMedianLds <= kTaskLds, "median LDS");
 
 // ------------------------------------------------------- per-phase kernels
 template <class Src>
@@ -2430,8 +2530,9 @@ __global__ __launch_bounds__(kWG) void k_pyramid(Src src)
     ph_pyramid(src(job), tile);
 }
 
+// (two 1024-thread workgroups per CU: 64 registers)
 template <class Src, int NT>
-__global__ __launch_bounds__(NT) void k_setup(Src src)
+__global__ __launch_bounds__(NT, NT == kAuxWG ? 8 : 4) void k_setup(Src src)
 {
     __shared__ __align__(16) unsigned char smem[(kMaxCells + 8 + NT) * 4];
     int job, tile;
@@ -2473,7 +2574,7 @@ __global__ __launch_bounds__(kWG) void k_tri(Src src)
 template <class Src, int NT>
 __global__ __launch_bounds__(NT) void k_stereo_c(Src src)
 {
-    __shared__ __align__(16) unsigned char smem[(256 + NT + 8) * 4 + (kMaxKp + 32) / 32 * 4];
+    __shared__ __align__(16) unsigned char smem[kMedianLds];
     int job, tile;
     if (!src.locate(PH_STEREO_C, job, tile)) return;
     task_stereo_c<NT>(src(job), tile, smem);
