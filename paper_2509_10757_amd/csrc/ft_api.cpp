@@ -1380,11 +1380,13 @@ ft_status ft_search_last_frame(ft_context *ctx, void *stream, const ft_last_poin
     J.direction = params->direction;
     J.check_rot = rot ? 1 : 0;
     J.rot_bins = params->bins;
-    // the window's levels are not centred on a predicted level: one-bin index
-    J.lv_lo = kLevels;
-    J.lv_hi = kLevels;
+    // Without a direction of motion a point searches its octave and the two beside
+    // it: an index with one bin per octave, as for predicted levels; with one, up
+    // to all levels on one side: one bin.
+    J.lv_lo = J.lv_hi = params->direction == 0 ? 1 : kLevels;
+    J.setup_split = setup_split(1);
     if ((st = build_view(ctx, J, 0, 0, cam, kps, u_right, preassigned, grid, out, ctx->direct))) return st;
-    HIP_TRY(ctx, launch_last_frame(J, 4, (hipStream_t)stream));
+    HIP_TRY(ctx, launch_last_frame(J, (hipStream_t)stream));
     return FT_OK;
 }
 

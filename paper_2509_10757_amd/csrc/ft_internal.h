@@ -202,9 +202,9 @@ static_assert(kPhases == PH_COUNT, "one timing slot per phase");
 // `totals` holds the number of workgroups of each phase.
 hipError_t launch_pipeline(const DevJob *table, const TileMap &map, const int32_t totals[PH_COUNT],
                            const DevJob &one, const Shapes &shapes, hipStream_t stream, hipEvent_t *ev);
-// Last-frame search of one job's view 0: setup, search (`lanes` per point),
-// claim resolution with the rotation histogram, rotation check and outputs.
-hipError_t launch_last_frame(const DevJob &J, int lanes, hipStream_t stream);
+// Last-frame search of one job's view 0: setup, search, claims, rotation check
+// and outputs.
+hipError_t launch_last_frame(const DevJob &J, hipStream_t stream);
 // Batch kernel of every phase for these shapes (JobTable argument), and its
 // workgroup size: the nodes of a lane's batch graph.
 void batch_kernels(const Shapes &shapes, void *fn[PH_COUNT], int block[PH_COUNT]);

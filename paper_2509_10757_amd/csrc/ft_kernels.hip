@@ -1942,6 +1942,81 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+// --------------------------------- last-frame search by projection
+// Initial Pose Estimation projects the last frame's matched map points into
+// the current frame and searches its keypoints (Section II-C); the same
+// search by projection as the local-map search (Section IV-E), with the
+// window taken from the last-frame keypoint (radius th * sf[octave], levels
+// by the direction of motion) instead of the predicted level, no ratio test,
+// and a rotation-consistency check over the frame's matches.
+//
+// Camera projection of a world point into view V (pinhole binary32, KB
+// binary64 rounded to binary32); false when the point is behind the camera
+// or outside the image bounds.
+__device__ __forceinline__ bool project_point(const DevView &V, float X, float Y, float Z, float &u, float &v,
+                                              float &zc)
+{
+    const float xc = ((V.R[0] * X + V.R[1] * Y) + V.R[2] * Z) + V.t[0];
+    const float yc = ((V.R[3] * X + V.R[4] * Y) + V.R[5] * Z) + V.t[1];
+    zc = ((V.R[6] * X + V.R[7] * Y) + V.R[8] * Z) + V.t[2];
+    u = 0.0f;
+    v = 0.0f;
+    if (!(zc > 0.0f)) return false;
+    if (V.model == FT_CAMERA_PINHOLE) {
+        u = ((V.fx * xc) / zc) + V.cx;
+        v = ((V.fy * yc) / zc) + V.cy;
+    } else {
+        const float kb[8] = {V.fx, V.fy, V.cx, V.cy, V.k[0], V.k[1], V.k[2], V.k[3]};
+        const double Pc[3] = {(double)xc, (double)yc, (double)zc};
+        double uv[2];
+        kb_project(kb, Pc, uv);
+        u = (float)uv[0];
+        v = (float)uv[1];
+    }
+    return u >= V.min_x && u <= V.max_x && v >= V.min_y && v <= V.max_y;
+}
+
+// What one last-frame point looks for: its projection and window.  The index's
+// level bins are those of the points' octaves (when it has them).
+__device__ __forceinline__ Query make_last_query(const DevJob &J, const DevView &V, int i)
+{
+    Query q;
+    const float X = J.pos[3 * i], Y = J.pos[3 * i + 1], Z = J.pos[3 * i + 2];
+    const int ol = lvl(J.l_oct[i]);
+    q.dm = load_desc(J.mdesc, i);
+    float zc;
+    q.vis = project_point(V, X, Y, Z, q.u, q.v, zc);
+    if (!q.vis) return q;
+    q.Rm = J.th * J.sf[ol];
+    q.plo = J.direction > 0 ? ol : J.direction < 0 ? 0 : ol - 1;
+    q.phi = J.direction > 0 ? kLevels - 1 : J.direction < 0 ? ol : ol + 1;
+    q.gate = V.u_right != nullptr;
+    q.uR = q.gate ? q.u - V.bf * (1.0f / zc) : 0.0f;
+    // cells of u -+ (r + 0.01) bracket every candidate (as in the local search)
+    const float Rc = q.Rm + 0.01f;
+    q.cx0 = cell_coord(q.u - Rc, V.min_x, V.inv_cw, V.cols);
+    q.cx1 = cell_coord(q.u + Rc, V.min_x, V.inv_cw, V.cols);
+    q.cy0 = cell_coord(q.v - Rc, V.min_y, V.inv_ch, V.rows);
+    q.cy1 = cell_coord(q.v + Rc, V.min_y, V.inv_ch, V.rows);
+    q.cb = (V.n_pb > 1 ? ol : 0) * (V.cols * V.rows);
+    return q;
+}
+
+// Acceptance and claim of a last-frame point's best candidate key (distance,
+// keypoint, level: 32 bits).
+__device__ __forceinline__ void finish_last(const DevJob &J, const DevView &V, int i, uint32_t key)
+{
+    if (i >= J.nM) return;
+    int k = -1, h = -1;
+    if (key != 0xFFFFFFFFu && (int)(key >> 20) <= J.th_high) {
+        h = (int)(key >> 20);
+        k = (int)((key >> 4) & 0xFFFFu);
+    }
+    V.mp_k[i] = k;
+    V.mp_h[i] = h;
+    if (k >= 0) atomicMin(&V.claim[k], ((uint32_t)h << 23) | (uint32_t)i);
+}
+
 // Record-dealt search (one lane per map point).  Every lane projects its map
 // point and loads the record ranges of up to kDealRows window rows at once;
 // the wave then lays the records of all 64 windows end to end and deals them
@@ -1962,7 +2037,9 @@ constexpr int kDealSeg = kDealTb + 128 * 4;               // record offset of ea
 constexpr int kDealCands = kDealSeg + 64 * kDealRows * 4;  // candidate list [64 * kDealRecs], or the round's marks
 constexpr int kDealLdsPerWave = kDealCands + 64 * kDealRecs * 4;
 
-// The wave takes map points m0 .. m0 + 63 of the view; `base` is its LDS.
+// The wave takes map points (kLast: last-frame points) m0 .. m0 + 63 of the view;
+// `base` is its LDS.
+template <bool kLast>
 __device__ __forceinline__ void ph_search_deal(const DevJob &J, const DevView &V, int m0, unsigned char *base)
 {
     const int lane = threadIdx.x & 63;
@@ -1977,7 +2054,7 @@ __device__ __forceinline__ void ph_search_deal(const DevJob &J, const DevView &V
 
     Query q;
     q.vis = false;
-    if (m < J.nM) q = make_query(J, V, m);
+    if (m < J.nM) q = kLast ? make_last_query(J, V, m) : make_query(J, V, m);
     const int cx0 = q.vis ? q.cx0 : 0, cx1 = q.vis ? q.cx1 : 0;
     const int cy0 = q.vis ? q.cy0 : 0, cy1 = q.vis ? q.cy1 : -1;
     const FT_G int32_t *off = V.cell_off + (q.vis ? q.cb : 0);
@@ -2100,8 +2177,12 @@ __device__ __forceinline__ void ph_search_deal(const DevJob &J, const DevView &V
         }
     }
     wave_lds_sync();
-    Top2<uint64_t> top = {key32_to_64(tb[lane]), key32_to_64(tb[64 + lane])};
-    finish_query<1>(J, V, m, 0, top);
+    if constexpr (kLast) {
+        finish_last(J, V, m, tb[lane]);
+    } else {
+        Top2<uint64_t> top = {key32_to_64(tb[lane]), key32_to_64(tb[64 + lane])};
+        finish_query<1>(J, V, m, 0, top);
+    }
 }
 
 // Search by projection, kWG-thread tiles, G lanes per map point, records read
@@ -2138,143 +2219,6 @@ __device__ __forceinline__ void ph_search_final(const DevJob &J, const DevView &
     if ((threadIdx.x & 63) == 0 && mk) atomicAdd(V.n_matches, (int)__popcll(mk));
 }
 
-// --------------------------------- last-frame search by projection
-// Initial Pose Estimation projects the last frame's matched map points into
-// the current frame and searches its keypoints (Section II-C); the same
-// search by projection as the local-map search (Section IV-E), with the
-// window taken from the last-frame keypoint (radius th * sf[octave], levels
-// by the direction of motion) instead of the predicted level, no ratio test,
-// and a rotation-consistency check over the frame's matches.
-//
-// Camera projection of a world point into view V (pinhole binary32, KB
-// binary64 rounded to binary32); false when the point is behind the camera
-// or outside the image bounds.
-__device__ __forceinline__ bool project_point(const DevView &V, float X, float Y, float Z, float &u, float &v,
-                                              float &zc)
-{
-    const float xc = ((V.R[0] * X + V.R[1] * Y) + V.R[2] * Z) + V.t[0];
-    const float yc = ((V.R[3] * X + V.R[4] * Y) + V.R[5] * Z) + V.t[1];
-    zc = ((V.R[6] * X + V.R[7] * Y) + V.R[8] * Z) + V.t[2];
-    u = 0.0f;
-    v = 0.0f;
-    if (!(zc > 0.0f)) return false;
-    if (V.model == FT_CAMERA_PINHOLE) {
-        u = ((V.fx * xc) / zc) + V.cx;
-        v = ((V.fy * yc) / zc) + V.cy;
-    } else {
-        const float kb[8] = {V.fx, V.fy, V.cx, V.cy, V.k[0], V.k[1], V.k[2], V.k[3]};
-        const double Pc[3] = {(double)xc, (double)yc, (double)zc};
-        double uv[2];
-        kb_project(kb, Pc, uv);
-        u = (float)uv[0];
-        v = (float)uv[1];
-    }
-    return u >= V.min_x && u <= V.max_x && v >= V.min_y && v <= V.max_y;
-}
-
-struct LastQuery {
-    bool in;            // projected inside the image
-    bool gate;          // stereo right-coordinate gate applies
-    float u, v, r, uR;
-    int lmin, lmax;     // keypoint levels searched
-    int cx0, cx1, cy0, cy1;
-    Desc d;
-};
-
-__device__ __forceinline__ LastQuery make_last_query(const DevJob &J, const DevView &V, int i)
-{
-    LastQuery q;
-    const float X = J.pos[3 * i], Y = J.pos[3 * i + 1], Z = J.pos[3 * i + 2];
-    const int ol = lvl(J.l_oct[i]);
-    q.d = load_desc(J.mdesc, i);
-    float zc;
-    q.in = project_point(V, X, Y, Z, q.u, q.v, zc);
-    if (!q.in) return q;
-    q.r = J.th * J.sf[ol];
-    if (J.direction > 0) {
-        q.lmin = ol;
-        q.lmax = kLevels - 1;
-    } else if (J.direction < 0) {
-        q.lmin = 0;
-        q.lmax = ol;
-    } else {
-        q.lmin = ol - 1;
-        q.lmax = ol + 1;
-    }
-    q.gate = V.u_right != nullptr;
-    q.uR = q.gate ? q.u - V.bf * (1.0f / zc) : 0.0f;
-    // cells of u -+ (r + 0.01) bracket every candidate (as in the local search)
-    const float Rc = q.r + 0.01f;
-    q.cx0 = cell_coord(q.u - Rc, V.min_x, V.inv_cw, V.cols);
-    q.cx1 = cell_coord(q.u + Rc, V.min_x, V.inv_cw, V.cols);
-    q.cy0 = cell_coord(q.v - Rc, V.min_y, V.inv_ch, V.rows);
-    q.cy1 = cell_coord(q.v + Rc, V.min_y, V.inv_ch, V.rows);
-    return q;
-}
-
-// Best candidate key (distance << 40 | keypoint << 8 | level) of one point
-// over the window's cells of the one-bin index; lane `sub` of G takes every
-// G-th record of each window row.
-template <int G>
-__device__ __forceinline__ uint64_t scan_last(const DevView &V, const LastQuery &q, int sub)
-{
-    uint64_t best = ~0ull;
-    const FT_G int32_t *off = V.cell_off;
-    for (int cy = q.cy0; cy <= q.cy1; ++cy) {
-        const int c0 = off[cy * V.cols + q.cx0], c1 = off[cy * V.cols + q.cx1 + 1];
-        for (int p0 = c0 + sub; p0 < c1; p0 += kSearchUnroll * G) {
-            CellRec rec[kSearchUnroll];
-            bool cand[kSearchUnroll];
-            Desc d[kSearchUnroll];
-            float ur[kSearchUnroll];
-            _Pragma("unroll") for (int e = 0; e < kSearchUnroll; ++e) rec[e] = V.crec[min(p0 + e * G, c1 - 1)];
-            _Pragma("unroll") for (int e = 0; e < kSearchUnroll; ++e)
-            {
-                const int ok = (int)(rec[e].meta & 0xFFu);
-                cand[e] = p0 + e * G < c1 && ok >= q.lmin && ok <= q.lmax && fabsf(rec[e].x - q.u) < q.r &&
-                          fabsf(rec[e].y - q.v) < q.r && !(rec[e].meta & 0x100u);
-                ur[e] = 0.0f;
-                if (cand[e]) {
-                    d[e] = load_desc(V.kdesc, (int)(rec[e].meta >> 16));
-                    if (q.gate) ur[e] = V.u_right[rec[e].meta >> 16];
-                }
-            }
-            _Pragma("unroll") for (int e = 0; e < kSearchUnroll; ++e)
-            {
-                const bool rej = q.gate && ur[e] > 0.0f && !(fabsf(q.uR - ur[e]) <= q.r);
-                if (cand[e] && !rej) best = min(best, cand_key(hamming(q.d, d[e]), rec[e].meta));
-            }
-        }
-    }
-    return best;
-}
-
-// G lanes per last-frame point: best candidate, acceptance, claim.
-template <int G>
-__device__ __forceinline__ void ph_last_search(const DevJob &J, const DevView &V, int tile)
-{
-    const int sub = threadIdx.x % G;
-    const int i = tile * (kWG / G) + threadIdx.x / G;
-    uint64_t best = ~0ull;
-    if (i < J.nM) {
-        const LastQuery q = make_last_query(J, V, i);
-        if (q.in) best = scan_last<G>(V, q, sub);
-    }
-    for (int o = 1; o < G; o <<= 1) {
-        const uint64_t other = shfl_xor64(best, o);
-        best = other < best ? other : best;
-    }
-    if (sub != 0 || i >= J.nM) return;
-    int k = -1, h = -1;
-    if (best != ~0ull && (int)(best >> 40) <= J.th_high) {
-        h = (int)(best >> 40);
-        k = (int)((best >> 8) & 0xFFFFu);
-    }
-    V.mp_k[i] = k;
-    V.mp_h[i] = h;
-    if (k >= 0) atomicMin(&V.claim[k], ((uint32_t)h << 23) | (uint32_t)i);
-}
-
 // Rotation bin of a match: last minus current orientation, plus 360 when
 // negative, rounded to one of `bins` equal bins, taken modulo `bins` (the one
 // past the last is bin 0).
@@ -2288,65 +2232,128 @@ __device__ __forceinline__ int rotation_bin(float a_last, float a_cur, int bins)
     return bin;
 }
 
-// Thread per point: the claim winners keep their keypoint (mp_k, distance |
-// bin << 16 in mp_h; losers get -1) and count their rotation bin.
-__device__ __forceinline__ void ph_last_resolve(const DevJob &J, const DevView &V, int tile)
+// Bins kept by the rotation check (bit b set), from the count of bin `lane` in
+// every lane: the fullest bin and, while holding a tenth of it, the second and
+// third fullest; ties to the lower bin.
+__device__ __forceinline__ uint64_t kept_bins(int count)
 {
-    const int i = tile * kWG + threadIdx.x;
-    if (i >= J.nM) return;
-    const int k = V.mp_k[i];
-    const int h = V.mp_h[i];
-    const bool keep = k >= 0 && V.claim[k] == (((uint32_t)h << 23) | (uint32_t)i);
-    int bin = 0;
-    if (keep && J.check_rot) {
-        bin = rotation_bin(J.l_ang[i], J.k_ang[k], J.rot_bins);
-        atomicAdd(&V.hist[bin], 1);
+    const int lane = threadIdx.x & 63;
+    int key = count > 0 ? (count << 6) | (63 - lane) : 0;   // (at most 2^23 points)
+    int top[3];
+    _Pragma("unroll") for (int t = 0; t < 3; ++t)
+    {
+        top[t] = wave_last(wave_inclusive_max(key));
+        key = key == top[t] ? 0 : key;
     }
-    V.mp_k[i] = keep ? k : -1;
-    V.mp_h[i] = keep ? (h | (bin << 16)) : -1;
+    const int m1 = top[0] >> 6, m2 = top[1] >> 6, m3 = top[2] >> 6;
+    uint64_t kept = 0;
+    if (m1 > 0) kept |= 1ull << (63 - (top[0] & 63));
+    if (m2 > 0 && 10 * (int64_t)m2 >= m1) {
+        kept |= 1ull << (63 - (top[1] & 63));
+        if (m3 > 0 && 10 * (int64_t)m3 >= m1) kept |= 1ull << (63 - (top[2] & 63));
+    }
+    return kept;
 }
 
-// Bins kept by the rotation check (bit b set): the fullest bin and, while
-// holding a tenth of it, the second and third fullest; ties to the lower bin.
-__device__ __forceinline__ uint64_t kept_bins(const DevView &V, int bins)
+// Claims, rotation check and outputs of up to kSortUnroll * NT points in one
+// workgroup (the points stay in registers, the histogram and the surviving
+// points' bits in LDS).
+constexpr int kLastFinishLds = kRotBinsMax * 4 + kSortUnroll * kAuxWG / 8 + 64 * 4;
+
+template <int NT>
+__device__ __forceinline__ void ph_last_finish(const DevJob &J, const DevView &V, int nK, unsigned char *smem)
 {
-    int i1 = -1, i2 = -1, i3 = -1, m1 = 0, m2 = 0, m3 = 0;
-    for (int b = 0; b < bins; ++b) {
-        const int c = V.hist[b];
-        if (c > m1) {
-            m3 = m2;
-            i3 = i2;
-            m2 = m1;
-            i2 = i1;
-            m1 = c;
-            i1 = b;
-        } else if (c > m2) {
-            m3 = m2;
-            i3 = i2;
-            m2 = c;
-            i2 = b;
-        } else if (c > m3) {
-            m3 = c;
-            i3 = b;
+    int *hist = reinterpret_cast<int *>(smem);
+    uint64_t *alive = reinterpret_cast<uint64_t *>(hist + kRotBinsMax);
+    int *found = reinterpret_cast<int *>(alive + kSortUnroll * NT / 64);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nM = J.nM;
+    if (tid < kRotBinsMax) hist[tid] = 0;
+    __syncthreads();
+    int k[kSortUnroll], h[kSortUnroll], bin[kSortUnroll];
+    uint32_t cl[kSortUnroll];
+    _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
+    {
+        const int i = tid + e * NT;
+        k[e] = i < nM ? V.mp_k[i] : -1;
+        h[e] = i < nM ? V.mp_h[i] : -1;
+    }
+    _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
+    {
+        const int i = tid + e * NT;
+        const bool q = k[e] >= 0;
+        float al = 0.0f, ak = 0.0f;
+        cl[e] = q ? V.claim[k[e]] : 0u;
+        if (q && J.check_rot) {
+            al = J.l_ang[i];
+            ak = J.k_ang[k[e]];
+        }
+        bin[e] = q && J.check_rot ? rotation_bin(al, ak, J.rot_bins) : 0;
+    }
+    _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
+    {
+        const int i = tid + e * NT;
+        if (k[e] >= 0 && cl[e] != (((uint32_t)h[e] << 23) | (uint32_t)i)) k[e] = -1;
+        if (k[e] >= 0 && J.check_rot) atomicAdd(&hist[bin[e]], 1);
+    }
+    __syncthreads();
+    const uint64_t kept = J.check_rot ? kept_bins(hist[lane]) : ~0ull;
+    _Pragma("unroll") for (int e = 0; e < kSortUnroll; ++e)
+    {
+        const int i = tid + e * NT;
+        const bool a = k[e] >= 0 && ((kept >> bin[e]) & 1ull);
+        const uint64_t m = __ballot(a);
+        if (lane == 0) alive[e * (NT / 64) + wave] = m;
+        if (i < nM) {
+            V.mp_match[i] = a ? k[e] : -1;
+            V.mp_dist[i] = a ? h[e] : -1;
         }
     }
-    if (10 * m2 < m1) {
-        i2 = -1;
-        i3 = -1;
-    } else if (10 * m3 < m1) {
-        i3 = -1;
+    __syncthreads();
+    int n = 0;
+    for (int idx = tid; idx < nK; idx += NT) {
+        const uint32_t c = V.claim[idx];
+        const int i = (int)(c & 0x7FFFFFu);
+        const bool has = c != 0xFFFFFFFFu && ((alive[i >> 6] >> (i & 63)) & 1ull);
+        V.kp_match[idx] = has ? i : -1;
+        n += has ? 1 : 0;
     }
-    uint64_t kept = 0;
-    if (i1 >= 0) kept |= 1ull << i1;
-    if (i2 >= 0) kept |= 1ull << i2;
-    if (i3 >= 0) kept |= 1ull << i3;
-    return kept;
+    n = wave_last(wave_inclusive_scan(n));
+    if (lane == 0) found[wave] = n;
+    __syncthreads();
+    if (tid < 64) {
+        n = wave_last(wave_inclusive_scan(tid < NT / 64 ? found[tid] : 0));
+        if (tid == 0) *V.n_matches = n;
+    }
+}
+
+// More points: thread per point: the claim winners keep their keypoint (mp_k,
+// distance | bin << 16 in mp_h; losers get -1) and count their rotation bin, in
+// LDS first (one global update per bin and workgroup).
+__device__ __forceinline__ void ph_last_resolve(const DevJob &J, const DevView &V, int tile, int *hist)
+{
+    const int i = tile * kWG + threadIdx.x;
+    if (threadIdx.x < kRotBinsMax) hist[threadIdx.x] = 0;
+    __syncthreads();
+    if (i < J.nM) {
+        const int k = V.mp_k[i];
+        const int h = V.mp_h[i];
+        const bool keep = k >= 0 && V.claim[k] == (((uint32_t)h << 23) | (uint32_t)i);
+        int bin = 0;
+        if (keep && J.check_rot) {
+            bin = rotation_bin(J.l_ang[i], J.k_ang[k], J.rot_bins);
+            atomicAdd(&hist[bin], 1);
+        }
+        V.mp_k[i] = keep ? k : -1;
+        V.mp_h[i] = keep ? (h | (bin << 16)) : -1;
+    }
+    __syncthreads();
+    if (threadIdx.x < kRotBinsMax && hist[threadIdx.x]) atomicAdd(&V.hist[threadIdx.x], hist[threadIdx.x]);
 }
 
 // Thread per point / keypoint: the rotation check and the outputs.
 __device__ __forceinline__ void ph_last_final(const DevJob &J, const DevView &V, int nK, int tile)
 {
-    const uint64_t kept = J.check_rot ? kept_bins(V, J.rot_bins) : ~0ull;
+    const uint64_t kept = J.check_rot ? kept_bins(V.hist[threadIdx.x & 63]) : ~0ull;
     auto alive = [&](int i) {
         return V.mp_k[i] >= 0 && ((kept >> ((V.mp_h[i] >> 16) & 63)) & 1ull);
     };
@@ -2503,7 +2510,7 @@ __device__ __forceinline__ void task_search(const DevJob &J, int tile, unsigned 
     const int tpv = search_tiles_per_view(J, G);
     const int v = tile / tpv;
     if (v >= J.n_views) return;
-    if constexpr (G == 1) ph_search_deal(J, J.view[v], (tile - v * tpv) * 64, smem);
+    if constexpr (G == 1) ph_search_deal<false>(J, J.view[v], (tile - v * tpv) * 64, smem);
     else ph_search<G>(J, J.view[v], tile - v * tpv);
 }
 
@@ -2609,24 +2616,34 @@ __global__ __launch_bounds__(kWG) void k_search_final(Src src)
     task_search_final(src(job), tile);
 }
 
-// Last-frame search (one view of one job): search, claim resolution with the
-// rotation histogram, rotation check and outputs.
-template <class Src, int G>
-__global__ __launch_bounds__(kWG) void k_last_search(Src src)
+// Last-frame search (one view of one job): search, then claims, rotation check
+// and outputs in one workgroup, or in two kernels for many points.
+template <class Src>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_last_search(Src src)
 {
+    __shared__ __align__(16) unsigned char smem[kDealLdsPerWave];
     int job, tile;
     if (!src.locate(PH_SEARCH, job, tile)) return;
     const DevJob &J = src(job);
-    ph_last_search<G>(J, J.view[0], tile);
+    ph_search_deal<true>(J, J.view[0], tile * 64, smem);
+}
+
+template <class Src>
+__global__ __launch_bounds__(kAuxWG) void k_last_finish(Src src)
+{
+    __shared__ __align__(16) unsigned char smem[kLastFinishLds];
+    const DevJob &J = src(0);
+    ph_last_finish<kAuxWG>(J, J.view[0], view_kp(J, 0), smem);
 }
 
 template <class Src>
 __global__ __launch_bounds__(kWG) void k_last_resolve(Src src)
 {
+    __shared__ int hist[kRotBinsMax];
     int job, tile;
     if (!src.locate(PH_SEARCH_FIN, job, tile)) return;
     const DevJob &J = src(job);
-    ph_last_resolve(J, J.view[0], tile);
+    ph_last_resolve(J, J.view[0], tile, hist);
 }
 
 template <class Src>
@@ -2638,33 +2655,26 @@ __global__ __launch_bounds__(kWG) void k_last_final(Src src)
     ph_last_final(J, J.view[0], view_kp(J, 0), tile);
 }
 
-hipError_t launch_last_frame(const DevJob &J, int lanes, hipStream_t s)
+hipError_t launch_last_frame(const DevJob &J, hipStream_t s)
 {
     OneJob src{J};
     void *args[] = {&src};
     const int nK = view_kp(J, 0);
-    // setup: the view's one-bin cell index, claims cleared, histogram and
-    // match count zeroed
-    hipError_t e = hipLaunchKernel(reinterpret_cast<void *>(&k_setup<OneJob, kWG>), dim3(1), dim3(kWG), args, 0, s);
+    auto launch = [&](auto *fn, int grid, int block) {
+        return hipLaunchKernel(reinterpret_cast<void *>(fn), dim3(grid), dim3(block), args, 0, s);
+    };
+    // setup: the view's cell index, claims cleared, histogram and match count zeroed
+    hipError_t e = launch(&k_setup<OneJob, kAuxWG>, setup_parts_view(J, 0), kAuxWG);
     if (e != hipSuccess) return e;
-    if (J.nM > 0) {
-        void *fn;
-        switch (lanes) {
-        case 1: fn = reinterpret_cast<void *>(&k_last_search<OneJob, 1>); break;
-        case 2: fn = reinterpret_cast<void *>(&k_last_search<OneJob, 2>); break;
-        case 8: fn = reinterpret_cast<void *>(&k_last_search<OneJob, 8>); break;
-        default: fn = reinterpret_cast<void *>(&k_last_search<OneJob, 4>); lanes = 4; break;
-        }
-        if ((e = hipLaunchKernel(fn, dim3(div_up(J.nM, kWG / lanes)), dim3(kWG), args, 0, s)) != hipSuccess) return e;
-        if ((e = hipLaunchKernel(reinterpret_cast<void *>(&k_last_resolve<OneJob>), dim3(div_up(J.nM, kWG)),
-                                 dim3(kWG), args, 0, s)) != hipSuccess)
-            return e;
-    }
-    const int n = J.nM > nK ? J.nM : nK;
-    if (n > 0 && (e = hipLaunchKernel(reinterpret_cast<void *>(&k_last_final<OneJob>), dim3(div_up(n, kWG)),
-                                      dim3(kWG), args, 0, s)) != hipSuccess)
-        return e;
-    return hipGetLastError();
+    if (J.nM > 0 && (e = launch(&k_last_search<OneJob>, div_up(J.nM, 64), 64)) != hipSuccess) return e;
+    // One workgroup holds kSortUnroll points per thread; a last frame has at most
+    // its keypoints' number of points, far fewer (1153 points and 1200 keypoints:
+    // 4 us against 14 us for the two kernels, whose launches and histogram
+    // updates it saves; keypoints are strided, so their number is bounded where
+    // more workgroups would be faster).
+    if (J.nM <= kSortUnroll * kAuxWG && nK <= 4 * kSortUnroll * kAuxWG) return launch(&k_last_finish<OneJob>, 1, kAuxWG);
+    if (J.nM > 0 && (e = launch(&k_last_resolve<OneJob>, div_up(J.nM, kWG), kWG)) != hipSuccess) return e;
+    return launch(&k_last_final<OneJob>, div_up(J.nM > nK ? J.nM : nK, kWG), kWG);
 }
 
 // ---------------------------------------------------- local-map edit
