@@ -380,9 +380,10 @@ typedef struct ft_map_edit {
  * `map` holds device arrays with room for `capacity` points; map->n (host) is
  * set to n1 + insert.n when the call returns, while the moves run on `stream`
  * (the map must not be read on another stream before they complete; host
- * insert arrays must stay unchanged until then).  The (slot, source) pairs
- * are read by the move kernel from the context's pinned staging, so an edit
- * enqueues two kernels and no copy.  With `edit->ids` the removals are point
+ * insert arrays must stay unchanged until then).  The tail slots' targets are
+ * read by the edit kernel from the context's pinned staging, so an edit enqueues
+ * one kernel and no copy (two kernels when the inserted points lie in the map's
+ * own arrays).  With `edit->ids` the removals are point
  * ids, and slot_id / slot_of are updated on the host for the moved, removed
  * and inserted points only (time proportional to the edit).
  * Errors: a repeated or out-of-range index (or id: outside [0, id_count), not

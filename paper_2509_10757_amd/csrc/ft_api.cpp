@@ -67,6 +67,13 @@ struct BatchGraph {
     bool off[PH_COUNT] = {};         // phase nodes disabled for the last submission (no tiles)
 };
 
+// One validated map edit: the removed slots, the (hole, source)
+// pairs, and the new count; nothing is changed until it is committed.
+struct PreparedEdit {
+    int n1 = 0, m = 0, n_holes = 0;
+    std::vector<int32_t> rem, pairs;
+};
+
 struct Lane {  // one batch in flight
     std::vector<Slot> slots;
     BatchGraph g;
@@ -115,6 +122,8 @@ struct ft_context {
     size_t edit_ring_bytes = 0, edit_head = 0;
     std::deque<EditChunk> edit_live;
     std::vector<hipEvent_t> edit_free_ev, edit_all_ev;
+    PreparedEdit edit_one;         // scratch of ft_map_update
+    std::vector<int32_t> edit_holes;    // scratch of the edit being prepared
     std::vector<uint64_t> edit_marks;   // removed-slot bitmap of the edit being prepared (left all zero)
     // ORB detection: per-tile look-back state and a ticket counter, one set
     // per call in flight (round robin; a set is reused once the event after
@@ -1392,13 +1401,6 @@ ft_status ft_search_last_frame(ft_context *ctx, void *stream, const ft_last_poin
 
 namespace {
 
-// One validated map edit: the removed slots (ascending), the (hole, source)
-// pairs, and the new count; nothing is changed until it is committed.
-struct PreparedEdit {
-    int n1 = 0, m = 0, n_holes = 0;
-    std::vector<int32_t> rem, pairs;
-};
-
 ft_status prepare_edit(ft_context *ctx, const ft_map_points *map, int32_t capacity, const ft_map_edit *edit,
                        PreparedEdit &pe)
 {
@@ -1497,8 +1499,8 @@ ft_status prepare_edit(ft_context *ctx, const ft_map_points *map, int32_t capaci
         return fail(ctx, FT_ERR_CAPACITY, "map update: %d points exceed the capacity %d", n1 + m, capacity);
     }
     // (hole, source) pairs: removed slots below n1 and surviving points from n1 up, both ascending
-    std::vector<int32_t> holes;
-    holes.reserve(nr);
+    std::vector<int32_t> &holes = ctx->edit_holes;
+    holes.clear();
     for (int w = 0; w < (n1 + 63) / 64; ++w) {
         uint64_t bits = mk[w];
         if (w == n1 / 64) bits &= (n1 % 64) ? ((1ull << (n1 % 64)) - 1) : 0ull;
@@ -1528,6 +1530,20 @@ ft_status prepare_edit(ft_context *ctx, const ft_map_points *map, int32_t capaci
     pe.m = m;
     pe.n_holes = n_holes;
     return FT_OK;
+}
+
+// Does any insert array overlap the map's array of the same or another field?
+bool map_overlaps(const ft_map_points &map, int32_t capacity, const ft_map_points &ins)
+{
+    const size_t width[5] = {12, 12, 4, 4, 32};
+    const void *m[5] = {map.pos, map.normal, map.dmin, map.dmax, map.desc};
+    const void *i[5] = {ins.pos, ins.normal, ins.dmin, ins.dmax, ins.desc};
+    for (int f = 0; f < 5; ++f)
+        for (int g = 0; g < 5; ++g) {
+            const uintptr_t a = (uintptr_t)m[f], b = (uintptr_t)i[g];
+            if (a < b + width[g] * (size_t)ins.n && b < a + width[f] * (size_t)capacity) return true;
+        }
+    return false;
 }
 
 // The id record follows an enqueued edit (removed ids leave, moved ids take
@@ -1590,13 +1606,15 @@ ft_status ft_map_update(ft_context *ctx, void *stream, ft_map_points *map, int32
 {
     ft_status st = enter(ctx);
     if (st) return st;
-    PreparedEdit pe;
+    PreparedEdit &pe = ctx->edit_one;
     if ((st = prepare_edit(ctx, map, capacity, edit, pe))) return st;
-    const size_t need = align_up(sizeof(int32_t) * 2 * (size_t)std::max(pe.n_holes, 1), 256);
+    const int tail = map->n - pe.n1;   // slots above the new count of survivors
+    const size_t need = align_up(sizeof(int32_t) * (size_t)std::max(tail, 1), 256);
     size_t off = 0;
     if ((st = take_edit_chunk(ctx, need, &off))) return st;
-    int32_t *pairs = reinterpret_cast<int32_t *>(ctx->edit_ring + off);
-    if (pe.n_holes) memcpy(pairs, pe.pairs.data(), sizeof(int32_t) * pe.pairs.size());
+    int32_t *holes = reinterpret_cast<int32_t *>(ctx->edit_ring + off);
+    std::fill(holes, holes + tail, -1);
+    for (int h = 0; h < pe.n_holes; ++h) holes[pe.pairs[2 * h + 1] - pe.n1] = pe.pairs[2 * h];
     hipStream_t s = (hipStream_t)stream;
     MapEditArgs a{};
     a.pos = const_cast<float *>(map->pos);
@@ -1604,8 +1622,8 @@ ft_status ft_map_update(ft_context *ctx, void *stream, ft_map_points *map, int32
     a.dmin = const_cast<float *>(map->dmin);
     a.dmax = const_cast<float *>(map->dmax);
     a.desc = const_cast<uint8_t *>(map->desc);
-    a.pairs = pairs;                  // pinned staging, read by the move kernel over the bus
-    a.n_pairs = pe.n_holes;
+    a.holes = holes;                  // pinned staging, read by the kernel over the bus
+    a.n_tail = pe.n_holes > 0 ? tail : 0;
     a.ipos = edit->insert.pos;
     a.inormal = edit->insert.normal;
     a.idmin = edit->insert.dmin;
@@ -1613,6 +1631,13 @@ ft_status ft_map_update(ft_context *ctx, void *stream, ft_map_points *map, int32
     a.idesc = edit->insert.desc;
     a.n1 = pe.n1;
     a.n_insert = pe.m;
+    if (a.n_tail > 0 && pe.m > 0 && map_overlaps(*map, capacity, edit->insert)) {
+        // points inserted from the map's own arrays: every move before any append
+        a.n_insert = 0;
+        HIP_TRY(ctx, launch_map_edit(a, s));
+        a.n_insert = pe.m;
+        a.n_tail = 0;
+    }
     HIP_TRY(ctx, launch_map_edit(a, s));
     if ((st = finish_edit_chunk(ctx, off, need, s))) return st;
     commit_record(edit, pe);

@@ -217,14 +217,14 @@ void batch_kernels(const Shapes &shapes, void *fn[PH_COUNT], int block[PH_COUNT]
 constexpr size_t kNoallocScratchBytes = FT_NOALLOC_SCRATCH_BYTES;
 hipError_t noalloc_scratch(int device, char **out, bool *gfx950);
 
-// Local-map edit (ft_kernels.hip): the (hole, source) pairs move first, then
-// the inserted points are appended at n1 (two launches: an append may land on
-// a source slot).
+// Local-map edit (ft_kernels.hip): the surviving points of the slots n1 ..
+// n1 + n_tail - 1 move to their holes and the inserted points take the slots
+// from n1 up, in one launch (the insert arrays must not overlap the map's).
 struct MapEditArgs {
     FT_G float *pos, *normal, *dmin, *dmax;
     FT_G uint8_t *desc;
-    const FT_G int32_t *pairs;   // [n_pairs][2]: hole, source
-    int32_t n_pairs;
+    const FT_G int32_t *holes;   // [n_tail]: hole of the point at n1 + i, -1 when that point is removed
+    int32_t n_tail;
     const FT_G float *ipos, *inormal, *idmin, *idmax;
     const FT_G uint8_t *idesc;
     int32_t n1, n_insert;

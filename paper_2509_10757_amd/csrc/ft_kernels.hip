@@ -2678,51 +2678,63 @@ hipError_t launch_last_frame(const DevJob &J, hipStream_t s)
 }
 
 // ---------------------------------------------------- local-map edit
-// A thread per moved or appended point copies its 64-byte record (position,
-// normal, distance bounds, descriptor).
-__device__ __forceinline__ void map_copy_rec(const MapEditArgs &a, int to, const FT_G float *pos,
-                                             const FT_G float *normal, const FT_G float *dmin,
-                                             const FT_G float *dmax, const FT_G uint8_t *desc, int from)
+// One point's 64-byte record (position, normal, distance bounds, descriptor).
+struct MapRec {
+    float p[3], nr[3], d0, d1;
+    v4u q0, q1;
+};
+
+__device__ __forceinline__ MapRec load_rec(const FT_G float *pos, const FT_G float *normal, const FT_G float *dmin,
+                                           const FT_G float *dmax, const FT_G uint8_t *desc, int i)
 {
-    float p[3], nr[3];
+    MapRec r;
     _Pragma("unroll") for (int c = 0; c < 3; ++c)
     {
-        p[c] = pos[3 * from + c];
-        nr[c] = normal[3 * from + c];
+        r.p[c] = pos[3 * i + c];
+        r.nr[c] = normal[3 * i + c];
     }
-    const float d0 = dmin[from], d1 = dmax[from];
-    const uint4 q0 = reinterpret_cast<const FT_G uint4 *>(desc + 32 * (size_t)from)[0];
-    const uint4 q1 = reinterpret_cast<const FT_G uint4 *>(desc + 32 * (size_t)from)[1];
-    _Pragma("unroll") for (int c = 0; c < 3; ++c)
-    {
-        a.pos[3 * to + c] = p[c];
-        a.normal[3 * to + c] = nr[c];
-    }
-    a.dmin[to] = d0;
-    a.dmax[to] = d1;
-    reinterpret_cast<FT_G uint4 *>(a.desc + 32 * (size_t)to)[0] = q0;
-    reinterpret_cast<FT_G uint4 *>(a.desc + 32 * (size_t)to)[1] = q1;
+    r.d0 = dmin[i];
+    r.d1 = dmax[i];
+    r.q0 = reinterpret_cast<const FT_G v4u *>(desc + 32 * (size_t)i)[0];
+    r.q1 = reinterpret_cast<const FT_G v4u *>(desc + 32 * (size_t)i)[1];
+    return r;
 }
 
-__global__ __launch_bounds__(kWG) void k_map_move(MapEditArgs a)
+__device__ __forceinline__ void store_rec(const MapEditArgs &a, int i, const MapRec &r)
+{
+    _Pragma("unroll") for (int c = 0; c < 3; ++c)
+    {
+        a.pos[3 * i + c] = r.p[c];
+        a.normal[3 * i + c] = r.nr[c];
+    }
+    a.dmin[i] = r.d0;
+    a.dmax[i] = r.d1;
+    reinterpret_cast<FT_G v4u *>(a.desc + 32 * (size_t)i)[0] = r.q0;
+    reinterpret_cast<FT_G v4u *>(a.desc + 32 * (size_t)i)[1] = r.q1;
+}
+
+// A thread per tail slot n1 + i: the surviving point it holds moves to its hole
+// below n1 (a slot no other thread touches), then inserted point i takes the
+// slot.  Both records are read before either is written, so one launch does
+// what moves and appends in two had to order.  What bounds it is the launch and
+// the holes' trip over the bus.
+__global__ __launch_bounds__(kWG) void k_map_edit(MapEditArgs a)
 {
     const int i = blockIdx.x * kWG + threadIdx.x;
-    if (i >= a.n_pairs) return;
-    const int hole = a.pairs[2 * i], src = a.pairs[2 * i + 1];
-    map_copy_rec(a, hole, a.pos, a.normal, a.dmin, a.dmax, a.desc, src);
-}
-
-__global__ __launch_bounds__(kWG) void k_map_append(MapEditArgs a)
-{
-    const int j = blockIdx.x * kWG + threadIdx.x;
-    if (j >= a.n_insert) return;
-    map_copy_rec(a, a.n1 + j, a.ipos, a.inormal, a.idmin, a.idmax, a.idesc, j);
+    const int hole = i < a.n_tail ? a.holes[i] : -1;
+    MapRec old, in;
+    if (i < a.n_insert) in = load_rec(a.ipos, a.inormal, a.idmin, a.idmax, a.idesc, i);
+    if (hole >= 0) {
+        old = load_rec(a.pos, a.normal, a.dmin, a.dmax, a.desc, a.n1 + i);
+        store_rec(a, hole, old);
+    }
+    if (i < a.n_insert) store_rec(a, a.n1 + i, in);
 }
 
 hipError_t launch_map_edit(const MapEditArgs &a, hipStream_t s)
 {
-    if (a.n_pairs > 0) hipLaunchKernelGGL(k_map_move, dim3(div_up(a.n_pairs, kWG)), dim3(kWG), 0, s, a);
-    if (a.n_insert > 0) hipLaunchKernelGGL(k_map_append, dim3(div_up(a.n_insert, kWG)), dim3(kWG), 0, s, a);
+    const int n = std::max(a.n_tail, a.n_insert);
+    if (n > 0) hipLaunchKernelGGL(k_map_edit, dim3(div_up(n, kWG)), dim3(kWG), 0, s, a);
     return hipGetLastError();
 }
 
