@@ -2200,23 +2200,54 @@ __device__ __forceinline__ void ph_search(const DevJob &J, const DevView &V, int
     finish_query<G>(J, V, m, sub, top);
 }
 
+constexpr int kFinalPer = 4;   // map points and keypoints per thread of the search resolve
+
+// Duplicate resolution and outputs: kFinalPer consecutive map points and
+// keypoints per thread, their loads together.
 __device__ __forceinline__ void ph_search_final(const DevJob &J, const DevView &V, int nK, int tile)
 {
-    const int idx = tile * kWG + threadIdx.x;
-    if (idx < J.nM) {
-        const int k = V.mp_k[idx];
-        const bool keep = k >= 0 && V.claim[k] == (((uint32_t)V.mp_h[idx] << 23) | (uint32_t)idx);
-        V.mp_match[idx] = keep ? k : -1;
-        V.mp_dist[idx] = keep ? V.mp_h[idx] : -1;
+    const int i0 = (tile * kWG + (int)threadIdx.x) * kFinalPer;
+    auto load = [](const FT_G int32_t *p, int i, int n, int r[kFinalPer]) {
+        if (i + kFinalPer <= n) {
+            const v4u v = *reinterpret_cast<const FT_G v4u_dw *>(p + i);
+            _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e) r[e] = (int)v[e];
+        } else {
+            _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e) r[e] = i + e < n ? p[i + e] : -1;
+        }
+    };
+    auto store = [](FT_G int32_t *p, int i, int n, const int r[kFinalPer]) {
+        if (i + kFinalPer <= n) {
+            *reinterpret_cast<FT_G v4u_dw *>(p + i) = v4u{(uint32_t)r[0], (uint32_t)r[1], (uint32_t)r[2], (uint32_t)r[3]};
+        } else {
+            _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e) if (i + e < n) p[i + e] = r[e];
+        }
+    };
+    int k[kFinalPer], h[kFinalPer], c[kFinalPer];
+    load(V.mp_k, i0, J.nM, k);
+    load(V.mp_h, i0, J.nM, h);
+    load(reinterpret_cast<const FT_G int32_t *>(V.claim), i0, nK, c);
+    if (i0 < J.nM) {
+        uint32_t cl[kFinalPer];
+        _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e) cl[e] = k[e] >= 0 ? V.claim[k[e]] : 0u;
+        _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e)
+        {
+            const bool keep = k[e] >= 0 && cl[e] == (((uint32_t)h[e] << 23) | (uint32_t)(i0 + e));
+            k[e] = keep ? k[e] : -1;
+            h[e] = keep ? h[e] : -1;
+        }
+        store(V.mp_match, i0, J.nM, k);
+        store(V.mp_dist, i0, J.nM, h);
     }
-    bool has = false;
-    if (idx < nK) {
-        const uint32_t c = V.claim[idx];
-        has = c != 0xFFFFFFFFu;
-        V.kp_match[idx] = has ? (int)(c & 0x7FFFFFu) : -1;
+    int n = 0;   // (an unclaimed keypoint's claim is ~0, as is what lies past the last)
+    _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e)
+    {
+        const bool has = c[e] != -1;
+        n += has ? 1 : 0;
+        c[e] = has ? (c[e] & 0x7FFFFF) : -1;
     }
-    const unsigned long long mk = __ballot(has);
-    if ((threadIdx.x & 63) == 0 && mk) atomicAdd(V.n_matches, (int)__popcll(mk));
+    if (i0 < nK) store(V.kp_match, i0, nK, c);
+    n = wave_last(wave_inclusive_scan(n));
+    if ((threadIdx.x & 63) == 0 && n) atomicAdd(V.n_matches, n);
 }
 
 // Rotation bin of a match: last minus current orientation, plus 360 when
@@ -2386,7 +2417,7 @@ __host__ __device__ inline int search_tiles_per_view(const DevJob &J, int lanes)
 __host__ __device__ inline int final_tiles_view(const DevJob &J, int v)
 {
     const int nK = view_kp(J, v);
-    return div_up(J.nM > nK ? J.nM : nK, kWG);
+    return div_up(J.nM > nK ? J.nM : nK, kWG * kFinalPer);
 }
 
 // Workgroups of the setup phase: J.setup_split for the row sort by level and
@@ -2448,17 +2479,24 @@ struct JobTable : BatchArgs {
     __device__ __forceinline__ const DevJob &operator()(int i) const { return p[i]; }
     __device__ __forceinline__ bool locate(int ph, int &job, int &tile) const
     {
-        const int32_t *pre = map.prefix + ph * (map.n_jobs + 1);
+        const FT_G int32_t *pre = map.prefix + ph * (map.n_jobs + 1);
         const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-        int lo = 0, hi = map.n_jobs;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (pre[mid] <= b) lo = mid;
-            else hi = mid;
+        const int lane = threadIdx.x & 63, n = map.n_jobs;
+        // The job is the number of prefix ends at or below b: 64 of them are
+        // compared per load (one round trip for up to 64 jobs, two for up to
+        // 4096, instead of one per step of a bisection).
+        int j0 = 0, below = 0;   // first job of the 64 compared, tiles before it
+        if (n > 64) {
+            const int e = 64 * (lane + 1);
+            const int v = pre[min(e, n)];
+            j0 = 64 * (int)__popcll(__ballot(e <= n && v <= b));
+            below = j0 ? __builtin_amdgcn_readlane(v, (j0 >> 6) - 1) : 0;
         }
-        job = lo;
-        tile = b - pre[lo];
-        return tile < pre[lo + 1] - pre[lo];
+        const int v = pre[min(j0 + lane + 1, n)];
+        const int k = (int)__popcll(__ballot(j0 + lane < n && v <= b));
+        job = j0 + k;
+        tile = b - (k ? __builtin_amdgcn_readlane(v, (k - 1) & 63) : below);
+        return job < n;
     }
 };
 static_assert(sizeof(JobTable) == sizeof(BatchArgs), "graph nodes pass a BatchArgs as the JobTable argument");
