@@ -24,6 +24,7 @@ struct Slot {  // workspace of one frame
     int32_t *row_start, *best_j, *best_h, *h2, *sad, *flag, *qlist, *tlist, *counts;
     RowRec *rrec;
     uint8_t *tdesc;
+    uint32_t *tkey;
     float *uR, *depth, *xyz;
     MatchRec *mrec;
     uint32_t *claimR;
@@ -193,6 +194,7 @@ void carve_slot(Slot &s, char *base, Bump &b, const ft_limits &L)
     s.row_start = b.take<int32_t>(base, (size_t)kLevels * ((size_t)L.max_rows + 1));
     s.rrec = b.take<RowRec>(base, kp);
     s.tdesc = b.take<uint8_t>(base, 32 * kp);
+    s.tkey = b.take<uint32_t>(base, kp);
     s.best_j = b.take<int32_t>(base, kp);
     s.best_h = b.take<int32_t>(base, kp);
     s.mrec = b.take<MatchRec>(base, kp);
@@ -271,6 +273,7 @@ void bind_stereo_ws(DevJob &J, const Slot &s)
     J.row_start = s.row_start;
     J.rrec = s.rrec;
     J.tdesc = s.tdesc;
+    J.tkey = s.tkey;
     J.best_j = s.best_j;
     J.best_h = s.best_h;
     J.mrec = s.mrec;

@@ -18,7 +18,7 @@ constexpr int kMaxKp = 65535;
 constexpr int kMaxCellRep = 3;       // copies of a keypoint in a level-binned cell index (level window <= 3 octaves)
 constexpr int kMaxMap = (1 << 23) - 1;
 constexpr int kKnnQueriesPerWG = 32;  // fisheye all-pairs: queries per 256-thread subgroup (16-row MFMA blocks)
-constexpr int kKnnTilesInFlight = 8;  // fisheye all-pairs: target tiles whose descriptor loads a wave keeps in flight
+constexpr int kKnnTilesInFlight = 4;  // fisheye all-pairs: target tiles whose descriptor loads a wave keeps in flight
 constexpr int kRefinePerWG = 4;       // pinhole refinement: one wave per match
 constexpr int kRefineLds = 1024;      // bytes of LDS per refining wave (patch + strip)
 constexpr int kRefineQPerWG = 16;     // ... 11x11 window, +-5 shifts: four matches per wave
@@ -137,6 +137,7 @@ struct DevJob {
     FT_G int32_t *row_start;               // [n_lb][rows + 1] record offsets of (level bin, row)
     FT_G RowRec *rrec;                     // right keypoints sorted by row
     FT_G uint8_t *tdesc;                   // right descriptors in overlap order (fisheye)
+    FT_G uint32_t *tkey;                   // (256 + popcount) << 16 | position of each of them
     FT_G int32_t *best_j, *best_h, *h2, *sad, *flag, *qlist, *tlist, *counts;
     FT_G MatchRec *mrec;                   // pinhole: accepted best matches, counts[2] of them
     FT_G float *uR, *depth, *xyz;

@@ -634,12 +634,13 @@ __device__ __forceinline__ void ph_rowsort(const DevJob &J, int part, int parts,
 
 // ------------------------------------------- setup: overlap lists (fisheye)
 // Indices i < n with a <= x[i] <= b, in order, into out[]; with `desc`, their
-// descriptors in the same order into tdesc.  U keypoints per thread
+// descriptors in the same order into tdesc and their all-pairs keys (256 +
+// popcount) << 16 | position into tkey.  U keypoints per thread
 // and round, their loads together; a round's counts per (keypoint, wave) are
 // scanned by every wave after one barrier.
 template <int NT, int U>
 __device__ __forceinline__ int compact_range(const FT_G float *x, int n, float a, float b, FT_G int32_t *out,
-                                             const FT_G uint8_t *desc, FT_G uint8_t *tdesc, int *wcnt)
+                                             const FT_G uint8_t *desc, FT_G uint8_t *tdesc, FT_G uint32_t *tkey, int *wcnt)
 {
     constexpr int NW = NT / 64;
     static_assert(U * NW <= 64, "one lane per (keypoint, wave) count");
@@ -678,6 +679,9 @@ __device__ __forceinline__ int compact_range(const FT_G float *x, int n, float a
                 if (desc) {
                     dst[2 * (size_t)pos] = d[e][0];
                     dst[2 * (size_t)pos + 1] = d[e][1];
+                    int pop = 0;
+                    _Pragma("unroll") for (int w = 0; w < 4; ++w) pop += __popc(d[e][0][w]) + __popc(d[e][1][w]);
+                    tkey[pos] = ((256u + (uint32_t)pop) << 16) | (uint32_t)pos;
                 }
             }
         }
@@ -695,14 +699,14 @@ __device__ __forceinline__ void ph_overlap(const DevJob &J, int part, int *wcnt)
     const int tid = threadIdx.x;
     if (part == 0) {
         for (int i = tid; i < J.L.n; i += NT) J.flag[i] = 0;
-        const int nQ = compact_range<NT, kSortUnroll>(J.L.x, J.L.n, J.ovl[0], J.ovl[1], J.qlist, nullptr, nullptr, wcnt);
+        const int nQ = compact_range<NT, kSortUnroll>(J.L.x, J.L.n, J.ovl[0], J.ovl[1], J.qlist, nullptr, nullptr, nullptr, wcnt);
         if (tid == 0) {
             J.counts[0] = nQ;
             *J.o_nmatch = 0;
         }
     } else {
         for (int j = tid; j < J.R.n; j += NT) J.claimR[j] = 0xFFFFFFFFu;
-        const int nT = compact_range<NT, 2>(J.R.x, J.R.n, J.ovr[0], J.ovr[1], J.tlist, J.R.desc, J.tdesc, wcnt);
+        const int nT = compact_range<NT, 2>(J.R.x, J.R.n, J.ovr[0], J.ovr[1], J.tlist, J.R.desc, J.tdesc, J.tkey, wcnt);
         if (tid == 0) J.counts[1] = nT;
     }
 }
@@ -1041,16 +1045,17 @@ __device__ __forceinline__ void best_scan(const DevJob &J, const int *rs, const 
 }
 
 // ----------------------------- stereo_a (fisheye): all-pairs top-2 on MFMA
-// H(a, b) = (256 - <a, b>) / 2 for the +-1 expansions of two descriptors.
-// A workgroup owns 16 queries (one MFMA row block); its four waves take every
-// fourth 16-target tile; partial top-2 lists are merged in LDS.  Each lane
-// group g (lanes 16g..16g+15) supplies descriptor bytes 8g..8g+7 over the four
-// K-steps of v_mfma_i32_16x16x64_i8 (two bytes = sixteen int8 per step); the A
-// and B operands use the same byte-to-K assignment, so the dot product is the
-// full 256-term sum whatever order the hardware sums K in.
-// NT threads = NT / 256 independent subgroups of four waves; subgroup k of
-// tile t owns queries (t * NT / 256 + k) * 16 ... + 15.  `part` holds 128
-// words per subgroup.  Every thread reaches both barriers.
+// H(a, b) = popcount(a) + popcount(b) - 2 popcount(a & b), the last term an int8
+// dot product over the descriptors' bits.  An operand byte need not be 0 or 1: a
+// target's bit t of a byte enters as that bit in place, 2^t (bit 7 as -128), so
+// that four operand bytes are one masked descriptor word; a query's bit t enters
+// as -2^(7 - t) (bit 7 as 1), so every pair of set bits adds -128, exactly.  (A
+// +-1 expansion of both operands takes a table lookup per byte, 8 conflicting
+// LDS reads and their indices per lane and tile, against 16 masks.)
+// Each lane group g (lanes 16g..16g+15) supplies descriptor bytes 8g..8g+7 over
+// the four K-steps of v_mfma_i32_16x16x64_i8 (bits 4h .. 4h + 3 of the bytes of
+// one word per step); the A and B operands use the same bit-to-K assignment, so
+// the dot product is the full 256-term sum whatever order the hardware sums K in.
 // Top-2 of 32-bit keys by value (keys are distinct: they carry the target
 // index).  a <= b always holds, so the new second is the median of a, b and
 // the key, one v_med3_u32; the new best is min(a, key).
@@ -1062,30 +1067,62 @@ __device__ __forceinline__ void top2_push(uint32_t &a, uint32_t &b, uint32_t key
     a = min(a, key);
 }
 
-// +-1 bytes of 16 descriptor bits (two table entries per byte pair).
-__device__ __forceinline__ v4i expand16(const uint64_t *tab, uint32_t word, int half)
+// Target operand: bits 4 half .. 4 half + 3 of the word's bytes, in place.
+__device__ __forceinline__ v4i target_bits(uint32_t word, int half)
 {
-    const uint64_t lo = tab[(word >> (16 * half)) & 0xFF];
-    const uint64_t hi = tab[(word >> (16 * half + 8)) & 0xFF];
-    return v4i{(int)(uint32_t)lo, (int)(uint32_t)(lo >> 32), (int)(uint32_t)hi, (int)(uint32_t)(hi >> 32)};
+    v4i v;
+    _Pragma("unroll") for (int k = 0; k < 4; ++k) v[k] = (int)(word & (0x01010101u << (4 * half + k)));
+    return v;
+}
+
+// Query operand of the same bits: bit t as -2^(7 - t), bit 7 as 1 (a byte holds
+// 0 or 1 times 256 - 2^(7 - t), so the product never carries).
+__device__ __forceinline__ v4i query_bits(uint32_t word, int half)
+{
+    v4i v;
+    _Pragma("unroll") for (int k = 0; k < 4; ++k)
+    {
+        const int t = 4 * half + k;
+        v[k] = (int)(((word >> t) & 0x01010101u) * (t == 7 ? 1u : 256u - (128u >> t)));
+    }
+    return v;
+}
+
+// One halving step of the top-2 lists of 2 N rows over a row of 16 lanes: a lane
+// keeps N of them (the upper N when `upper`), gives the others to its partner
+// (DPP control kCtrl, an exchange with a lane of the other half) and merges what
+// the partner gives.
+template <int N, int kCtrl>
+__device__ __forceinline__ void top2_halve(uint32_t *ta, uint32_t *tb, bool upper)
+{
+    _Pragma("unroll") for (int i = 0; i < N; ++i)
+    {
+        const uint32_t ka = upper ? ta[i + N] : ta[i], kb = upper ? tb[i + N] : tb[i];
+        const uint32_t sa = upper ? ta[i] : ta[i + N], sb = upper ? tb[i] : tb[i + N];
+        const uint32_t oa = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sa, kCtrl, 0xF, 0xF, false);
+        const uint32_t ob = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sb, kCtrl, 0xF, 0xF, false);
+        const Top2<uint32_t> t = top2_merge(Top2<uint32_t>{ka, kb}, oa, ob);
+        ta[i] = t.a;
+        tb[i] = t.b;
+    }
 }
 
 // Fisheye all-pairs top-2 on the matrix cores.  A workgroup subgroup (256
 // threads) owns kKnnQueriesPerWG queries; its four waves split the target
-// tiles.  Each wave holds the +-1 expansion of all its queries (QB blocks of
-// 16) and expands every 16-target tile once for all QB blocks.
+// tiles, and the partial top-2 lists are merged in LDS (`part`: 4 x
+// kKnnQueriesPerWG x 2 words per subgroup).  Each wave holds the operands of all
+// its queries (QB blocks of 16) and expands every 16-target tile once for all QB
+// blocks.  Every thread reaches the barrier.
+// Bound by vector instructions (32 keys and 16 masks per lane and tile beside 8
+// MFMAs): 64 fisheye frames of 1500 keypoints 44.0 us with +-1 operands from a
+// table, a key assembled per column and shuffles at the end, 38.9 now; the mixed
+// 64-frame batch 167.4 -> 165.2.  Pushing a tile's keys while the next one's
+// MFMAs run takes 25 registers more and loses in the batch (168.5).
 template <int NT>
-__device__ __forceinline__ void ph_knn(const DevJob &J, int tile, uint64_t *tab, uint32_t *part)
+__device__ __forceinline__ void ph_knn(const DevJob &J, int tile, uint32_t *part)
 {
     constexpr int QB = kKnnQueriesPerWG / 16;
     const int tid = threadIdx.x, ltid = tid & 255, sg = tid >> 8;
-    // +-1 expansion of every byte value: bit t -> byte t, 1 -> +1, 0 -> -1
-    if (tid < 256) {
-        uint64_t e = 0;
-        for (int t = 0; t < 8; ++t) e |= (uint64_t)(((tid >> t) & 1) ? 0x01u : 0xFFu) << (8 * t);
-        tab[tid] = e;
-    }
-    __syncthreads();
     const int nQ = J.counts[0], nT = J.counts[1];
     const int q0 = (tile * (NT / 256) + sg) * kKnnQueriesPerWG;
     part += sg * (4 * kKnnQueriesPerWG * 2);
@@ -1095,61 +1132,55 @@ __device__ __forceinline__ void ph_knn(const DevJob &J, int tile, uint64_t *tab,
     v4i A[QB][4];
     _Pragma("unroll") for (int qb = 0; qb < QB; ++qb)
     {
+        // (queries past the last: no bits)
         const int qa = q0 + 16 * qb + c;
         uint2 w = make_uint2(0, 0);
         if (qa < nQ) w = *reinterpret_cast<const uint2 *>(J.L.desc + 32 * (size_t)J.qlist[qa] + 8 * g);
-        _Pragma("unroll") for (int s = 0; s < 4; ++s)
-        {
-            // the queries' signs are flipped (x ^ 0xFE negates a +-1 byte), so
-            // the MFMA accumulates -dot
-            const v4i e = expand16(tab, s < 2 ? w.x : w.y, s & 1);
-            const int f = (int)0xFEFEFEFE;
-            A[qb][s] = qa < nQ ? v4i{e[0] ^ f, e[1] ^ f, e[2] ^ f, e[3] ^ f} : v4i{0, 0, 0, 0};
-        }
+        _Pragma("unroll") for (int s = 0; s < 4; ++s) A[qb][s] = query_bits(s < 2 ? w.x : w.y, s & 1);
     }
-    uint32_t ta[QB][4], tb[QB][4];
-    _Pragma("unroll") for (int qb = 0; qb < QB; ++qb)
-        _Pragma("unroll") for (int r = 0; r < 4; ++r) ta[qb][r] = tb[qb][r] = 0xFFFFFFFFu;
+    uint32_t ta[QB * 4], tb[QB * 4];
+    _Pragma("unroll") for (int r = 0; r < QB * 4; ++r) ta[r] = tb[r] = 0xFFFFFFFFu;
     // (wave-uniform, so that the loop below branches on scalars)
     const int n_tiles = __builtin_amdgcn_readfirstlane((nT + 15) >> 4);
     const int wv = __builtin_amdgcn_readfirstlane(wave);
-    // A ring of kKnnTilesInFlight target tiles' descriptor bytes per wave: the
-    // loop is unrolled over the ring, and a slot is reloaded with the tile
-    // kKnnTilesInFlight steps ahead as soon as its bytes are expanded, so that
-    // several loads are in flight while the matrix cores work.
+    // A ring of kKnnTilesInFlight target tiles' descriptor bytes and keys per
+    // wave: the loop is unrolled over the ring, and a slot is reloaded with the
+    // tile kKnnTilesInFlight steps ahead as soon as its bytes are expanded, so
+    // that several loads are in flight while the matrix cores work.
     constexpr int D = kKnnTilesInFlight;
-    const uint8_t *tdesc = J.tdesc + 8 * g;
-    uint2 ring[D];
-    _Pragma("unroll") for (int d = 0; d < D; ++d)
-    {
-        const int tj = min(((wv + 4 * d) << 4) + c, nT - 1);
-        ring[d] = *reinterpret_cast<const uint2 *>(tdesc + 32 * (size_t)tj);
-    }
+    const FT_G uint8_t *tdesc = J.tdesc + 8 * g;
+    struct Slot {
+        uint2 w;
+        uint32_t key;
+    };
+    auto load = [&](int tj) {
+        tj = min(tj, nT - 1);
+        typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+        const v2u w = *reinterpret_cast<const FT_G v2u *>(tdesc + 32 * (size_t)tj);
+        return Slot{make_uint2(w[0], w[1]), J.tkey[tj]};
+    };
+    Slot ring[D];
+    _Pragma("unroll") for (int d = 0; d < D; ++d) ring[d] = load(((wv + 4 * d) << 4) + c);
     // one tile: expand its bytes from ring slot d (then refill the slot with
     // the tile D steps ahead), run the MFMAs, push the column's keys
-    auto step = [&](uint2 &slot, int t, bool refill) {
-        const int tj = (t << 4) + c;
-        const bool tv = tj < nT;
-        // (a column past the end holds the last target's bytes: its sums are
-        // computed and never pushed)
-        v4i B[4];
-        _Pragma("unroll") for (int s = 0; s < 4; ++s) B[s] = expand16(tab, s < 2 ? slot.x : slot.y, s & 1);
-        if (refill) slot = *reinterpret_cast<const uint2 *>(tdesc + 32 * (size_t)min(tj + 64 * D, nT - 1));
-        // acc[r] = -dot(query row 4g + r of block qb, target column c); the key
-        // (256 - dot) << 15 | index = Hamming << 16 | index (dot = 256 - 2 H) is
-        // kbase + (acc << 15), one shift-add.  The blocks' MFMA chains are
-        // interleaved so that each hides the other's latency.
-        const uint32_t kbase = (256u << 15) | (uint32_t)tj;
-        v4i acc[QB];
+    auto step = [&](Slot &slot, int t, bool refill) {
+        // (a column past the end holds the last target's bytes; its keys are above
+        // every other, and at least two targets are valid, so they never survive)
+        const uint32_t key = (t << 4) + c < nT ? slot.key : 0xC0000000u;
+        v4i B[4], acc[QB];
+        _Pragma("unroll") for (int s = 0; s < 4; ++s) B[s] = target_bits(s < 2 ? slot.w.x : slot.w.y, s & 1);
+        if (refill) slot = load((t << 4) + c + 64 * D);
+        // acc[r] = -128 popcount(a & b) of query row 4g + r of block qb and target
+        // column c, so key + (acc << 10) = (256 + H - popcount(a)) << 16 | position,
+        // one shift-add; the query's own count is added at the end.  The blocks'
+        // MFMA chains are interleaved so that each hides the other's latency.
         _Pragma("unroll") for (int qb = 0; qb < QB; ++qb) acc[qb] = v4i{0, 0, 0, 0};
         _Pragma("unroll") for (int s = 0; s < 4; ++s)
             _Pragma("unroll") for (int qb = 0; qb < QB; ++qb)
                 acc[qb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[qb][s], B[s], acc[qb], 0, 0, 0);
-        if (tv) {
-            _Pragma("unroll") for (int qb = 0; qb < QB; ++qb)
-                _Pragma("unroll") for (int r = 0; r < 4; ++r)
-                    top2_push(ta[qb][r], tb[qb][r], kbase + ((uint32_t)acc[qb][r] << 15));
-        }
+        _Pragma("unroll") for (int qb = 0; qb < QB; ++qb)
+            _Pragma("unroll") for (int r = 0; r < 4; ++r)
+                top2_push(ta[4 * qb + r], tb[4 * qb + r], key + ((uint32_t)acc[qb][r] << 10));
     };
     // whole turns of the ring (no exit inside, so the loads' waits stay
     // counted), then the last tiles with no refill
@@ -1158,17 +1189,22 @@ __device__ __forceinline__ void ph_knn(const DevJob &J, int tile, uint64_t *tab,
         _Pragma("unroll") for (int d = 0; d < D; ++d) step(ring[d], t0 + 4 * d, true);
     _Pragma("unroll") for (int d = 0; d < D - 1; ++d)
         if (t0 + 4 * d < n_tiles) step(ring[d], t0 + 4 * d, false);
-    _Pragma("unroll") for (int qb = 0; qb < QB; ++qb)
+    // The lists of the 8 rows (4 qb + r) merged over the 16 columns: lanes halve
+    // the rows they hold with the lane at c ^ 8, c ^ 7 and c ^ 3, so that lane c
+    // ends with row c >> 1, then merge with the lane at c ^ 1.
+    static_assert(QB == 2, "eight rows per lane");
+    top2_halve<4, 0x128>(ta, tb, c & 8);   // row_ror:8
+    top2_halve<2, 0x141>(ta, tb, c & 4);   // row_half_mirror
+    top2_halve<1, 0x1B>(ta, tb, c & 2);    // quad_perm 3,2,1,0
     {
-        _Pragma("unroll") for (int r = 0; r < 4; ++r)
-        {
-            Top2<uint32_t> t = {ta[qb][r], tb[qb][r]};
-            _Pragma("unroll") for (int m = 1; m < 16; m <<= 1) t = top2_merge(t, __shfl_xor(t.a, m), __shfl_xor(t.b, m));
-            if (c == 0) {
-                uint32_t *pw = part + (wave * kKnnQueriesPerWG + 16 * qb + 4 * g + r) * 2;
-                pw[0] = t.a;
-                pw[1] = t.b;
-            }
+        const uint32_t oa = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ta[0], 0xB1, 0xF, 0xF, false);   // quad_perm 1,0,3,2
+        const uint32_t ob = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)tb[0], 0xB1, 0xF, 0xF, false);
+        const Top2<uint32_t> t = top2_merge(Top2<uint32_t>{ta[0], tb[0]}, oa, ob);
+        const int r = c >> 1;
+        if ((c & 1) == 0) {
+            uint32_t *pw = part + (wave * kKnnQueriesPerWG + 16 * (r >> 2) + 4 * g + (r & 3)) * 2;
+            pw[0] = t.a;
+            pw[1] = t.b;
         }
     }
     }
@@ -1178,9 +1214,11 @@ __device__ __forceinline__ void ph_knn(const DevJob &J, int tile, uint64_t *tab,
         for (int w = 1; w < 4; ++w)
             t = top2_merge(t, part[(w * kKnnQueriesPerWG + ltid) * 2], part[(w * kKnnQueriesPerWG + ltid) * 2 + 1]);
         const int i = J.qlist[q0 + ltid];
+        const Desc d = load_desc(J.L.desc, i);
+        const int pop = hamming(d, Desc{make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)}) - 256;
         J.best_j[i] = J.tlist[t.a & 0xFFFFu];
-        J.best_h[i] = (int)(t.a >> 16);
-        J.h2[i] = (int)(t.b >> 16);
+        J.best_h[i] = (int)(t.a >> 16) + pop;
+        J.h2[i] = (int)(t.b >> 16) + pop;
     }
 }
 
@@ -2529,10 +2567,8 @@ __device__ __forceinline__ void task_setup(const DevJob &J, int tile, unsigned c
 template <int G>
 __device__ __forceinline__ void task_stereo_a(const DevJob &J, int tile, unsigned char *smem)
 {
-    uint64_t *tab = reinterpret_cast<uint64_t *>(smem);
-    uint32_t *part = reinterpret_cast<uint32_t *>(smem + 256 * sizeof(uint64_t));
     if (J.flags & JOB_STEREO_PINHOLE) ph_best<G>(J, tile);
-    else ph_knn<kWG>(J, tile, tab, part);
+    else ph_knn<kWG>(J, tile, reinterpret_cast<uint32_t *>(smem));
 }
 
 template <int NT>
@@ -2560,7 +2596,7 @@ __device__ __forceinline__ void task_search_final(const DevJob &J, int tile)
     ph_search_final(J, J.view[v], view_kp(J, v), tile - (v ? t0 : 0));
 }
 
-static_assert(256 * 8 + 4 * kKnnQueriesPerWG * 2 * 4 <= kTaskLds, "stereo_a LDS");
+static_assert(4 * kKnnQueriesPerWG * 2 * 4 <= kTaskLds, "stereo_a LDS");
 static_assert(kRefinePerWG * kRefineLds <= kTaskLds, "refine LDS");
 static_assert(kRefineQPerWG * kRefineQLds <= kTaskLds, "refine LDS (quarter waves)");
 static_assert(kDealLdsPerWave <= kTaskLds, "record-dealt search LDS");
@@ -2585,10 +2621,13 @@ __global__ __launch_bounds__(NT, NT == kAuxWG ? 8 : 4) void k_setup(Src src)
     task_setup<NT>(src(job), tile, smem);
 }
 
+// Five waves per SIMD: with four the mixed 64-frame batch takes 166.9 us instead
+// of 165.4 (its pinhole frames want the waves; a single fisheye frame is equal),
+// and six spill (191 and more).
 template <class Src, int G>
-__global__ __launch_bounds__(kWG) void k_stereo_a(Src src)
+__global__ __launch_bounds__(kWG, 5) void k_stereo_a(Src src)
 {
-    __shared__ __align__(16) unsigned char smem[256 * 8 + 4 * kKnnQueriesPerWG * 2 * 4];
+    __shared__ __align__(16) unsigned char smem[4 * kKnnQueriesPerWG * 2 * 4];
     int job, tile;
     if (!src.locate(PH_STEREO_A, job, tile)) return;
     task_stereo_a<G>(src(job), tile, smem);
