@@ -49,6 +49,12 @@ struct Desc {
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 // A dword at any byte address; four dwords from a dword boundary.
+// Constant address space: memory that no kernel running with the reader writes.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define FT_C __attribute__((address_space(4)))
+#else
+#define FT_C
+#endif
 typedef uint32_t u32_any __attribute__((aligned(1)));
 typedef v4u v4u_dw __attribute__((aligned(4)));
 
@@ -2514,7 +2520,16 @@ struct OneJob {
 };
 
 struct JobTable : BatchArgs {
-    __device__ __forceinline__ const DevJob &operator()(int i) const { return p[i]; }
+    // The table is constant while a kernel runs, and a tile's job is uniform: read
+    // from the constant address space its fields are scalar loads also behind the
+    // kernel's own stores (the compiler must otherwise take them for changed, and
+    // loads each through the vector units: 78 loads of the set-up, 19 of the
+    // refinement).  Mixed 64-frame batch 165.2 -> 154.2 us, 8 frames from images
+    // 76.8 -> 72.2.
+    __device__ __forceinline__ const DevJob &operator()(int i) const
+    {
+        return *(const DevJob *)((const FT_C DevJob *)p + i);
+    }
     __device__ __forceinline__ bool locate(int ph, int &job, int &tile) const
     {
         const FT_G int32_t *pre = map.prefix + ph * (map.n_jobs + 1);
