@@ -22,7 +22,6 @@ constexpr int kKnnTilesInFlight = 4;  // fisheye all-pairs: target tiles whose d
 constexpr int kRefinePerWG = 4;       // pinhole refinement: one wave per match
 constexpr int kRefineLds = 1024;      // bytes of LDS per refining wave (patch + strip)
 constexpr int kRefineQPerWG = 16;     // ... 11x11 window, +-5 shifts: four matches per wave
-constexpr int kRefineQLds = 800;      // bytes of LDS per match (11 x 12 + 11 x 24 16-bit values)
 constexpr int kMaxPyrW = 1536;        // widest level-0 image of the pyramid build (and of the ORB detector's LDS rows)
 constexpr int kRotBinsMax = 64;       // rotation histogram bins of the last-frame search
 

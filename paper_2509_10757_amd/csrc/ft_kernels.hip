@@ -1336,123 +1336,133 @@ __device__ __forceinline__ void ph_refine_wave(const DevJob &J, int tile, uint8_
     atomicMin(&J.claimR[j], ((uint32_t)bh << 23) | (uint32_t)i);
 }
 
-// The usual 11x11 window and +-5 shifts: four matches per wave, sixteen lanes
-// each; lane k of a match stages its share of the windows and computes SAD of
-// shift k - 5 alone, so the argmin is a 16-lane shuffle reduction.  A quarter
-// of the waves of the general path, the same dependent round trips.
-__device__ __forceinline__ void ph_refine_quarter(const DevJob &J, int tile, uint8_t *lds)
+// Sum of two lanes' packed 16-bit partial sums, halving the dwords a lane holds:
+// the upper N when `upper`; the others go to the partner of DPP control kCtrl.
+template <int N, int kCtrl>
+__device__ __forceinline__ void sums_halve(uint32_t *s, bool upper)
 {
-    constexpr int w = 5, L = 5, side = 2 * w + 1, strip = 2 * (L + w) + 1, nS = 2 * L + 1;
-    static_assert(side == 11 && strip == 21, "the row staging reads 11-byte patch and 21-byte strip rows");
-    static_assert((side * 12 + side * 24) * 2 <= kRefineQLds, "refine windows");
+    _Pragma("unroll") for (int i = 0; i < N; ++i)
+    {
+        const uint32_t keep = upper ? s[i + N] : s[i], give = upper ? s[i] : s[i + N];
+        s[i] = keep + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)give, kCtrl, 0xF, 0xF, false);
+    }
+}
+
+template <int kCtrl>
+__device__ __forceinline__ uint32_t min_dpp(uint32_t v)
+{
+    return min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xF, 0xF, false));
+}
+
+// The usual 11x11 window and +-5 shifts: four matches per wave, sixteen lanes
+// each.  Lane r < 11 holds row r of the patch and of the strip in registers (two
+// pixels per dword) and sums its row for all 11 shifts; the sums of the rows are
+// added by halving exchanges that leave lane k with the SAD of shift k - 5.
+// Two pixels per instruction, no LDS and no barrier, about 450 vector instructions
+// a wave (768 with the rows staged in LDS as 16-bit pairs, read back per shift).
+// One frame of 1200 keypoints 39.2 -> 36.9 us, the mixed 64-frame batch 154.2 ->
+// 151.2; in 64 pinhole frames the kernel takes 32 us (36.7 before), where the
+// window rows, a cache line each, are scattered over 140 MB of pyramids.
+__device__ __forceinline__ void ph_refine_quarter(const DevJob &J, int tile)
+{
+    constexpr int w = 5, L = 5, side = 2 * w + 1, nS = 2 * L + 1;
+    static_assert(side == 11 && nS == 11, "a row of 16 lanes: 11 window rows, then 11 shifts");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ql = lane & 15, slot = wave * 4 + (lane >> 4);
     const int idx = tile * kRefineQPerWG + slot;   // position in the frame's match list
     const bool has = idx < J.counts[2];
     const MatchRec mr = J.mrec[min(idx, max(J.L.n - 1, 0))];   // loaded with the list length
-    const int i = mr.i;
-    int j = -1, l = 0, su = 0, sv = 0, su0 = 0, Wl = 0, bh = 0;
-    float xi = 0.0f, sfl = 0.0f;
-    int64_t off = 0;
-    bool act = false;
-    if (has) {
-        // everything the match needs is in its list record: one round of loads
-        j = mr.j;
-        bh = mr.h;
-        const float xj = mr.bx;
-        xi = mr.x;
-        const float yi = mr.y;
-        l = lvl(mr.oct);
-        const float s = pick_level(J.inv_sf, l);
-        sfl = pick_level(J.sf, l);
-        su = (int)roundf(xi * s);
-        sv = (int)roundf(yi * s);
-        su0 = (int)roundf(xj * s);
-        Wl = pick_level(J.lv_w, l);
-        const int Hl = pick_level(J.lv_h, l);
-        off = pick_level(J.lv_off, l);
-        act = su - w >= 0 && su + w < Wl && sv - w >= 0 && sv + w < Hl && su0 - L - w >= 0 &&
-              su0 + L + w < Wl;
-    }
-    // Windows in LDS as 16-bit values, rows padded to whole dwords: the left
-    // patch holds P + 255, the right strip holds S.  For shift k (lane k) the
-    // centre-subtracted difference |(P - cL) - (S - cR)| equals
-    // |(P + 255) - (S + off)| with off = cL - cR + 255 in [0, 510]; both
-    // terms lie in [0, 765], so v_sad_u16 sums two pixels per instruction.
-    constexpr int pS = 12, sS = 24;   // row strides (u16) of patch and strip
-    uint16_t *P = reinterpret_cast<uint16_t *>(lds + slot * kRefineQLds);
-    uint16_t *S = P + side * pS;
-    if (act) {
-        // 22 row jobs per match (the patch's 11 rows, then the strip's), two
-        // per lane: each row read whole (unaligned dword loads covering exactly
-        // its 11 or 21 bytes) and widened to 16-bit pairs by byte permutes
-        const uint8_t *IL = J.pyrL + off;
-        const uint8_t *IR = J.pyrR + off;
-        constexpr uint32_t kLo = 0x0C010C00u, kHi = 0x0C030C02u;   // bytes 0,1 / 2,3 -> u16 pair
-        _Pragma("unroll") for (int h = 0; h < 2; ++h)
+    if (__ballot(has) == 0) return;   // (whole waves past the list's end)
+    // the level tables, a level per lane, read by the match's level from there
+    // (a select chain over 8 levels of 6 dwords takes 150 instructions)
+    static_assert(kLevels == 8, "a level table per 8 lanes");
+    const int tl = lane & 7;
+    const float t_inv = J.inv_sf[tl], t_sf = J.sf[tl];
+    const int t_w = J.lv_w[tl], t_h = J.lv_h[tl];
+    const int64_t t_off = J.lv_off[tl];
+    // everything the match needs is in its list record: one round of loads
+    const int i = mr.i, j = mr.j, bh = mr.h;
+    const float xi = mr.x;
+    const int l = lvl(mr.oct);
+    const float s = __shfl(t_inv, l), sfl = __shfl(t_sf, l);
+    const int Wl = __shfl(t_w, l), Hl = __shfl(t_h, l);
+    const int64_t off = ((int64_t)__shfl((int)(t_off >> 32), l) << 32) | (uint32_t)__shfl((int)t_off, l);
+    const int su = (int)roundf(xi * s), sv = (int)roundf(mr.y * s), su0 = (int)roundf(mr.bx * s);
+    const bool act = has && su - w >= 0 && su + w < Wl && sv - w >= 0 && sv + w < Hl && su0 - L - w >= 0 &&
+                     su0 + L + w < Wl;
+    // For shift k the centre-subtracted difference |(P - cL) - (S - cR)| equals
+    // |(P + 255) - (S + off_k)| with off_k = cL - cR + 255 in [0, 510]; both terms
+    // lie in [0, 765], so v_sad_u16 sums two pixels per instruction.
+    uint32_t sums[8];   // of shifts 2d, 2d + 1: each at most 120 * 510 over the window, 16 bits
+    _Pragma("unroll") for (int d = 0; d < 8; ++d) sums[d] = 0;
+    if (act && ql < side) {
+        const int64_t row = off + (int64_t)(sv - w + ql) * Wl;
+        const FT_G uint8_t *p = J.pyrL + row + (su - w);
+        const FT_G uint8_t *q = J.pyrR + row + (su0 - L - w);
+        // The aligned dwords that hold the row (misaligned loads take two to four
+        // times as long).  The strip's 21 bytes lie in six of them.  The patch's 11
+        // lie in three or four; a load of four begins with the first of them, so it
+        // may end up to 4 bytes behind the row's last dword, inside the next row of
+        // the window; the last row's load ends with its last dword and begins up to
+        // 5 bytes before the row, inside the row above.
+        const uint32_t ap = (uint32_t)reinterpret_cast<uintptr_t>(p) & 3u;
+        const uint32_t aq = (uint32_t)reinterpret_cast<uintptr_t>(q) & 3u;
+        const bool back = ql == side - 1 && ap < 2;
+        const v4u pd = *reinterpret_cast<const FT_G v4u_dw *>(p - ap - (back ? 4 : 0));
+        const v4u qd = *reinterpret_cast<const FT_G v4u_dw *>(q - aq);
+        typedef uint32_t v2u_dw __attribute__((ext_vector_type(2), aligned(4)));
+        const v2u_dw qe = *reinterpret_cast<const FT_G v2u_dw *>(q - aq + 16);
+        const uint32_t p0 = back ? pd[1] : pd[0], p1 = back ? pd[2] : pd[1], p2 = back ? pd[3] : pd[2];
+        const uint32_t pb[3] = {__builtin_amdgcn_alignbyte(p1, p0, ap), __builtin_amdgcn_alignbyte(p2, p1, ap),
+                                __builtin_amdgcn_alignbyte(pd[3], p2, ap)};
+        const uint32_t sd[7] = {qd[0], qd[1], qd[2], qd[3], qe[0], qe[1], 0u};
+        uint32_t sb[6];
+        _Pragma("unroll") for (int k = 0; k < 6; ++k) sb[k] = __builtin_amdgcn_alignbyte(sd[k + 1], sd[k], aq);
+        // pixel pairs: P of columns 2t, 2t + 1 plus 255 (the last of column 10 alone),
+        // E of strip columns 2t, 2t + 1, O of 2t + 1, 2t + 2
+        constexpr uint32_t kLo = 0x0C010C00u, kHi = 0x0C030C02u, kMid = 0x0C020C01u, kNext = 0x0C040C03u;
+        constexpr uint32_t k255 = 0x00FF00FFu;
+        const uint32_t P[6] = {__builtin_amdgcn_perm(0u, pb[0], kLo) + k255, __builtin_amdgcn_perm(0u, pb[0], kHi) + k255,
+                               __builtin_amdgcn_perm(0u, pb[1], kLo) + k255, __builtin_amdgcn_perm(0u, pb[1], kHi) + k255,
+                               __builtin_amdgcn_perm(0u, pb[2], kLo) + k255, ((pb[2] >> 16) & 255u) + 255u};
+        uint32_t E[11], O[10];
+        _Pragma("unroll") for (int t = 0; t < 5; ++t)
         {
-            const int jb = ql + 16 * h;
-            if (jb < side) {
-                const uint8_t *src = IL + (size_t)(sv - w + jb) * Wl + su - w;
-                uint32_t d0, d1;
-                uint16_t d2;
-                __builtin_memcpy(&d0, src, 4);
-                __builtin_memcpy(&d1, src + 4, 4);
-                __builtin_memcpy(&d2, src + 8, 2);
-                const uint32_t d3 = src[10];
-                uint32_t *row = reinterpret_cast<uint32_t *>(P + jb * pS);
-                constexpr uint32_t k255 = 0x00FF00FFu;
-                row[0] = __builtin_amdgcn_perm(0u, d0, kLo) + k255;
-                row[1] = __builtin_amdgcn_perm(0u, d0, kHi) + k255;
-                row[2] = __builtin_amdgcn_perm(0u, d1, kLo) + k255;
-                row[3] = __builtin_amdgcn_perm(0u, d1, kHi) + k255;
-                row[4] = __builtin_amdgcn_perm(0u, (uint32_t)d2, kLo) + k255;
-                row[5] = d3 + 255u;   // column 11 is padding
-            } else if (jb < 2 * side) {
-                const int r = jb - side;
-                const uint8_t *src = IR + (size_t)(sv - w + r) * Wl + su0 - L - w;
-                uint32_t d[5];
-                _Pragma("unroll") for (int k = 0; k < 5; ++k) __builtin_memcpy(&d[k], src + 4 * k, 4);
-                const uint32_t d5 = src[20];
-                uint32_t *row = reinterpret_cast<uint32_t *>(S + r * sS);
-                _Pragma("unroll") for (int k = 0; k < 5; ++k)
-                {
-                    row[2 * k] = __builtin_amdgcn_perm(0u, d[k], kLo);
-                    row[2 * k + 1] = __builtin_amdgcn_perm(0u, d[k], kHi);
-                }
-                row[10] = d5;
-            }
+            E[2 * t] = __builtin_amdgcn_perm(0u, sb[t], kLo);
+            E[2 * t + 1] = __builtin_amdgcn_perm(0u, sb[t], kHi);
+            O[2 * t] = __builtin_amdgcn_perm(0u, sb[t], kMid);
+            O[2 * t + 1] = __builtin_amdgcn_perm(sb[t + 1], sb[t], kNext);
+        }
+        E[10] = sb[5] & 255u;
+        // the centre row's pixels 5..15, one per shift, from lane 5 (row_newbcast:5)
+        auto centre = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x155, 0xF, 0xF, false); };
+        constexpr uint32_t kLoLo = 0x01000100u, kHiHi = 0x03020302u;
+        const uint32_t cl = centre(P[2]);
+        const uint32_t cL = __builtin_amdgcn_perm(cl, cl, kHiHi);   // cL + 255 in both halves
+        uint32_t c[6];
+        _Pragma("unroll") for (int t = 0; t < 6; ++t) c[t] = centre(E[t + 2]);
+        _Pragma("unroll") for (int k = 0; k < nS; ++k)
+        {
+            const uint32_t cc = c[(k + 1) >> 1];
+            const uint32_t o = cL - __builtin_amdgcn_perm(cc, cc, (k & 1) ? kLoLo : kHiHi);
+            const uint32_t *S = (k & 1) ? O + (k >> 1) : E + (k >> 1);
+            uint32_t acc = 0;
+            _Pragma("unroll") for (int t = 0; t < 5; ++t) acc = __builtin_amdgcn_sad_u16(P[t], S[t] + o, acc);
+            acc = __builtin_amdgcn_sad_u16(P[5], (uint32_t)(uint16_t)(S[5] + o), acc);   // column 10
+            if (k & 1) sums[k >> 1] |= acc << 16;
+            else sums[k >> 1] = acc;
         }
     }
-    __syncthreads();
-    int sad = 0;
-    uint32_t key = 0xFFFFFFFFu;   // SAD << 4 | lane: ties go to the smaller shift
-    if (act && ql < nS) {
-        const int cL = (int)P[w * pS + w] - 255;
-        const int cR = S[w * sS + ql + w];
-        const uint32_t off1 = (uint32_t)(cL - cR + 255);
-        const uint32_t off2 = off1 | (off1 << 16);
-        const int b0 = ql & ~1;                   // first u16 of the strip pairs read
-        const uint32_t sh = (uint32_t)(ql & 1) * 2;   // byte shift realigning them to pixel ql
-        uint32_t acc = 0;
-        _Pragma("unroll 1") for (int r = 0; r < side; ++r)
-        {
-            const uint32_t *pa = reinterpret_cast<const uint32_t *>(P + r * pS);
-            const uint32_t *pb = reinterpret_cast<const uint32_t *>(S + r * sS + b0);
-            uint32_t db[6];
-            _Pragma("unroll") for (int t = 0; t < 6; ++t) db[t] = pb[t];
-            _Pragma("unroll") for (int t = 0; t < 5; ++t)
-                acc = __builtin_amdgcn_sad_u16(pa[t], __builtin_amdgcn_alignbyte(db[t + 1], db[t], sh) + off2, acc);
-            const int d10 = (int)P[r * pS + 10] - ((int)S[r * sS + ql + 10] + (int)off1);
-            acc += (uint32_t)abs(d10);
-        }
-        sad = (int)acc;
-        key = ((uint32_t)sad << 4) | (uint32_t)ql;
-    }
-    for (int m = 8; m >= 1; m >>= 1) {
-        const uint32_t o = __shfl_xor(key, m);
-        key = o < key ? o : key;
-    }
+    // rows added with the lane at ql ^ 8, ^ 7, ^ 3 and ^ 1; lane ql ends with the
+    // dword of shifts ql & ~1, ql | 1
+    sums_halve<4, 0x128>(sums, ql & 8);   // row_ror:8
+    sums_halve<2, 0x141>(sums, ql & 4);   // row_half_mirror
+    sums_halve<1, 0x1B>(sums, ql & 2);    // quad_perm 3,2,1,0
+    const uint32_t both = sums[0] + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sums[0], 0xB1, 0xF, 0xF, false);   // quad_perm 1,0,3,2
+    const int sad = (int)((ql & 1) ? both >> 16 : both & 0xFFFFu);
+    // SAD << 4 | lane: ties go to the smaller shift
+    uint32_t key = act && ql < nS ? ((uint32_t)sad << 4) | (uint32_t)ql : 0xFFFFFFFFu;
+    key = min_dpp<0xB1>(min_dpp<0x1B>(min_dpp<0x141>(min_dpp<0x128>(key))));
     const int kb = (int)(key & 15u) - L;
     const int base = lane & ~15;
     const int a = __shfl(sad, base + max(kb + L - 1, 0));
@@ -1489,7 +1499,7 @@ __device__ __forceinline__ void ph_refine_quarter(const DevJob &J, int tile, uin
 
 __device__ __forceinline__ void ph_refine(const DevJob &J, int tile, uint8_t *lds)
 {
-    if (refine_quarter(J)) ph_refine_quarter(J, tile, lds);
+    if (refine_quarter(J)) ph_refine_quarter(J, tile);
     else ph_refine_wave(J, tile, lds);
 }
 
@@ -2613,7 +2623,6 @@ __device__ __forceinline__ void task_search_final(const DevJob &J, int tile)
 
 static_assert(4 * kKnnQueriesPerWG * 2 * 4 <= kTaskLds, "stereo_a LDS");
 static_assert(kRefinePerWG * kRefineLds <= kTaskLds, "refine LDS");
-static_assert(kRefineQPerWG * kRefineQLds <= kTaskLds, "refine LDS (quarter waves)");
 static_assert(kDealLdsPerWave <= kTaskLds, "record-dealt search LDS");
 static_assert(kMedianLds <= kTaskLds, "median LDS");
 
@@ -2649,14 +2658,11 @@ __global__ __launch_bounds__(kWG, 5) void k_stereo_a(Src src)
 }
 
 template <class Src>
-// 7 waves per SIMD (at most 72 registers) instead of the 6 its 73 registers
-// would give: more window loads in flight.  The batch kernel fits without a
-// spill; the single-frame one spills two values.
+// 7 waves per SIMD (at most 72 registers): more window loads in flight; 8 spill
+// and are no faster.
 __global__ __launch_bounds__(kWG, 7) void k_refine(Src src)
 {
-    __shared__ __align__(16) unsigned char smem[kRefineQPerWG * kRefineQLds > kRefinePerWG * kRefineLds
-                                                    ? kRefineQPerWG * kRefineQLds
-                                                    : kRefinePerWG * kRefineLds];
+    __shared__ __align__(16) unsigned char smem[kRefinePerWG * kRefineLds];
     int job, tile;
     if (!src.locate(PH_REFINE, job, tile)) return;
     ph_refine(src(job), tile, smem);
