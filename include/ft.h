@@ -187,7 +187,7 @@ typedef struct ft_fisheye_out {
 } ft_fisheye_out;
 
 /* Two nearest right keypoints (overlap region) of every overlap left keypoint
- * by Hamming distance, computed exactly as an int8 +-1 dot product on the
+ * by Hamming distance, computed exactly as an int8 dot product of the bits on the
  * matrix cores; a ratio test; a parallax, triangulation (linear least
  * squares, float64), positive-depth and reprojection check; duplicates
  * resolved.  Errors as for ft_stereo_match_pinhole. */

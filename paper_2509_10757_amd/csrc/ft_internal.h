@@ -173,7 +173,7 @@ struct Shapes {
 };
 
 // Tiles of each phase for each job, as prefix sums: batch launches map a flat
-// block index to (job, tile) with a binary search over them.
+// block index to (job, tile) by comparing 64 of them per load.
 struct TileMap {
     int32_t n_jobs;
     const FT_G int32_t *prefix;  // device [PH_COUNT][n_jobs + 1]

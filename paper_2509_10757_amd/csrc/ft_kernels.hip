@@ -13,8 +13,11 @@
 //              claim tables and counters
 //   stereo_a   pinhole best match: G lanes per left keypoint stream the
 //              row-sorted records of the rows that can hold a match
-//              | fisheye all-pairs top-2 on the matrix cores (int8 +-1 MFMA)
-//   refine     pinhole SAD refinement, one wave per match, patches in LDS
+//              | fisheye all-pairs top-2 on the matrix cores (int8 MFMA over the
+//              descriptors' bits)
+//   refine     pinhole SAD refinement: sixteen lanes per match, a window row per
+//              lane in registers (11x11, +-5 shifts); other windows one wave per
+//              match, patches in LDS
 //   tri        fisheye ratio + triangulation check (float64; its own kernel
 //              so that its register demand does not cap the refinement's
 //              occupancy)
@@ -1362,7 +1365,7 @@ __device__ __forceinline__ uint32_t min_dpp(uint32_t v)
 // a wave (768 with the rows staged in LDS as 16-bit pairs, read back per shift).
 // One frame of 1200 keypoints 39.2 -> 36.9 us, the mixed 64-frame batch 154.2 ->
 // 151.2; in 64 pinhole frames the kernel takes 32 us (36.7 before), where the
-// window rows, a cache line each, are scattered over 140 MB of pyramids.
+// window rows, a cache line each, fetch 106 MB.
 __device__ __forceinline__ void ph_refine_quarter(const DevJob &J, int tile)
 {
     constexpr int w = 5, L = 5, side = 2 * w + 1, nS = 2 * L + 1;
