@@ -844,7 +844,7 @@ def main():
         map_maint = {"workload": f"{n_map}-point local map, {n_edit} points removed and {n_edit} inserted per edit",
                      "edit_ms": percentiles(te), "whole_map_upload_ms": percentiles(tw),
                      "bytes_per_point": 64, "reps": reps,
-                     "timed": "host clock around each edit (removal list, both kernels, inserted points read "
+                     "timed": "host clock around each edit (removal list, the kernel, inserted points read "
                               "from pinned memory) and each whole-map upload (one gather copy), synchronized"}
         log("map maintenance", map_maint)
         del dmap, whole_dev
