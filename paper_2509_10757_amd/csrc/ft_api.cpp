@@ -513,8 +513,8 @@ void fill_search_common(DevJob &J, const ft_map_points *map, const ft_search_par
     J.r_wide = p->r_wide;
     J.dist_lo = p->dist_lo;
     J.dist_hi = p->dist_hi;
-    J.lv_lo = p->level_lo;
-    J.lv_hi = p->level_hi;
+    J.lv_lo = std::min(p->level_lo, kMaxWindow);
+    J.lv_hi = std::min(p->level_hi, kMaxWindow);
     J.th_high = p->th_high;
     J.s_ratio_num = p->ratio_num;
     J.s_ratio_den = p->ratio_den;

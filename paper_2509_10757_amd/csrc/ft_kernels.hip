@@ -2115,7 +2115,9 @@ __device__ __forceinline__ void ph_search_deal(const DevJob &J, const DevView &V
     const int cx0 = q.vis ? q.cx0 : 0, cx1 = q.vis ? q.cx1 : 0;
     const int cy0 = q.vis ? q.cy0 : 0, cy1 = q.vis ? q.cy1 : -1;
     const FT_G int32_t *off = V.cell_off + (q.vis ? q.cb : 0);
-    const int lv = q.vis ? ((q.plo + 16) | ((q.phi + 16) << 8)) : (16 | (15 << 8));
+    // the octave window's two ends as signed 16-bit halves (-kMaxWindow .. kLevels - 1 + kMaxWindow)
+    static_assert(kMaxWindow + kLevels <= 0x7FFF, "16-bit halves");
+    const int lv = q.vis ? (q.plo & 0xFFFF) | (int)((uint32_t)q.phi << 16) : (int)0xFFFF0000u;   // (else 0 .. -1: none)
     qp[lane] = make_float4(q.u, q.v, q.vis ? q.Rm : 0.0f, __int_as_float(lv));
     quR[lane] = q.vis ? q.uR : 0.0f;
     qd[lane] = q.dm;
@@ -2191,8 +2193,8 @@ __device__ __forceinline__ void ph_search_deal(const DevJob &J, const DevView &V
                     iq.u = qq.x;
                     iq.v = qq.y;
                     iq.Rm = qq.z;
-                    iq.plo = (l & 0xFF) - 16;
-                    iq.phi = ((l >> 8) & 0xFF) - 16;
+                    iq.plo = (int16_t)l;
+                    iq.phi = l >> 16;
                     if (in_window(iq, rec[k].x, rec[k].y, rec[k].meta)) {
                         cand[k] = (rec[k].meta >> 16) | ((rec[k].meta & 15u) << 16) | ((uint32_t)ml << 20);
                         ++nc;
