@@ -383,7 +383,11 @@ typedef struct ft_map_edit {
  * insert arrays must stay unchanged until then).  The tail slots' targets are
  * read by the edit kernel from the context's pinned staging, so an edit enqueues
  * one kernel and no copy (two kernels when the inserted points lie in the map's
- * own arrays).  With `edit->ids` the removals are point
+ * own arrays).  Inserted points in the map's own arrays are read after every move;
+ * they must lie outside the slots n1 .. n1 + insert.n - 1 that they are written
+ * to (a call whose inserted points overlap those slots copies some of them after
+ * they have been overwritten, in no order: it is not refused, and those slots'
+ * contents are undefined).  With `edit->ids` the removals are point
  * ids, and slot_id / slot_of are updated on the host for the moved, removed
  * and inserted points only (time proportional to the edit).
  * Errors: a repeated or out-of-range index (or id: outside [0, id_count), not
@@ -398,8 +402,10 @@ ft_status ft_map_update(ft_context *ctx, void *stream, ft_map_points *map, int32
 /* n edits of n distinct maps in one call (Update Local Map for every frame of
  * a batch): edits[i] is applied to *maps[i] (HOST array of pointers; each
  * map's n is updated) within capacities[i], with ft_map_update's rule and
- * checks.  Every edit is validated before anything is enqueued: on any error
- * no map, no id record changes and nothing is enqueued.  The edits' pairs and
+ * checks (inserted points in any of the maps' arrays are read after every map's
+ * moves, and must lie outside the slots that any of the edits appends to).
+ * Every edit is validated before anything is enqueued: on any error no map, no
+ * id record changes and nothing is enqueued.  The edits' pairs and
  * appends are staged together in the context's pinned staging, copied to the
  * device in one command, and applied by two kernels for all n maps.  Errors:
  * as ft_map_update, two edits naming one map or sharing an id record:

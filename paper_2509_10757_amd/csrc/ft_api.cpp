@@ -1636,6 +1636,7 @@ ft_status ft_map_update(ft_context *ctx, void *stream, ft_map_points *map, int32
     a.n_insert = pe.m;
     if (a.n_tail > 0 && pe.m > 0 && map_overlaps(*map, capacity, edit->insert)) {
         // points inserted from the map's own arrays: every move before any append
+        // (the caller keeps them outside the slots appended to)
         a.n_insert = 0;
         HIP_TRY(ctx, launch_map_edit(a, s));
         a.n_insert = pe.m;
