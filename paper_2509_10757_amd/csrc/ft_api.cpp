@@ -1611,7 +1611,8 @@ ft_status ft_map_update(ft_context *ctx, void *stream, ft_map_points *map, int32
     if (st) return st;
     PreparedEdit &pe = ctx->edit_one;
     if ((st = prepare_edit(ctx, map, capacity, edit, pe))) return st;
-    const int tail = map->n - pe.n1;   // slots above the new count of survivors
+    // slots above the new count of survivors (the kernel reads none when no hole takes one)
+    const int tail = pe.n_holes > 0 ? map->n - pe.n1 : 0;
     const size_t need = align_up(sizeof(int32_t) * (size_t)std::max(tail, 1), 256);
     size_t off = 0;
     if ((st = take_edit_chunk(ctx, need, &off))) return st;
@@ -1626,7 +1627,7 @@ ft_status ft_map_update(ft_context *ctx, void *stream, ft_map_points *map, int32
     a.dmax = const_cast<float *>(map->dmax);
     a.desc = const_cast<uint8_t *>(map->desc);
     a.holes = holes;                  // pinned staging, read by the kernel over the bus
-    a.n_tail = pe.n_holes > 0 ? tail : 0;
+    a.n_tail = tail;
     a.ipos = edit->insert.pos;
     a.inormal = edit->insert.normal;
     a.idmin = edit->insert.dmin;
