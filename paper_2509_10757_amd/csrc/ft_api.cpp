@@ -68,11 +68,12 @@ struct BatchGraph {
     bool off[PH_COUNT] = {};         // phase nodes disabled for the last submission (no tiles)
 };
 
-// One validated map edit: the removed slots, the (hole, source)
-// pairs, and the new count; nothing is changed until it is committed.
+// One validated map edit: the removed slots and the new counts; nothing is
+// changed until it is committed.
 struct PreparedEdit {
     int n1 = 0, m = 0, n_holes = 0;
-    std::vector<int32_t> rem, pairs;
+    std::vector<int32_t> rem;
+    std::vector<int32_t> pairs;   // [n_holes][2]: hole, source (an edit among several)
 };
 
 struct Lane {  // one batch in flight
@@ -123,8 +124,7 @@ struct ft_context {
     size_t edit_ring_bytes = 0, edit_head = 0;
     std::deque<EditChunk> edit_live;
     std::vector<hipEvent_t> edit_free_ev, edit_all_ev;
-    PreparedEdit edit_one;         // scratch of ft_map_update
-    std::vector<int32_t> edit_holes;    // scratch of the edit being prepared
+    PreparedEdit edit_one;              // scratch of ft_map_update (4 B per removal, at most max_map_points of them)
     std::vector<uint64_t> edit_marks;   // removed-slot bitmap of the edit being prepared (left all zero)
     // ORB detection: per-tile look-back state and a ticket counter, one set
     // per call in flight (round robin; a set is reused once the event after
@@ -1402,8 +1402,21 @@ ft_status ft_search_last_frame(ft_context *ctx, void *stream, const ft_last_poin
     return FT_OK;
 }
 
+}  // extern "C"
+
 namespace {
 
+// Clears the marks of the first `upto` removed slots, all that are set (whole
+// words: neighbouring slots would wait for one another's bits).
+void unmark_edit(ft_context *ctx, const PreparedEdit &pe, int upto)
+{
+    uint64_t *mk = ctx->edit_marks.data();
+    const int32_t *rem = pe.rem.data();
+    for (int i = 0; i < upto; ++i) mk[rem[i] >> 6] = 0;
+}
+
+// Validates an edit; on success its removed slots are marked in edit_marks (the
+// caller clears them when it has read the moves).
 ft_status prepare_edit(ft_context *ctx, const ft_map_points *map, int32_t capacity, const ft_map_edit *edit,
                        PreparedEdit &pe)
 {
@@ -1480,58 +1493,58 @@ ft_status prepare_edit(ft_context *ctx, const ft_map_points *map, int32_t capaci
     // also yields the holes below n1 in ascending order without a sort
     std::vector<uint64_t> &mk = ctx->edit_marks;
     if (mk.size() < (size_t)(n + 63) / 64) mk.resize((size_t)(n + 63) / 64, 0);
-    auto unmark = [&](int upto) {
-        for (int i = 0; i < upto; ++i) mk[rem[i] >> 6] &= ~(1ull << (rem[i] & 63));
-    };
     for (int i = 0; i < nr; ++i) {
         const int r = rem[i];
         if (r < 0 || r >= n) {
-            unmark(i);
+            unmark_edit(ctx, pe, i);
             return fail(ctx, FT_ERR_INVALID_ARGUMENT, "map update: index %d outside [0, %d)", r, n);
         }
         const uint64_t bit = 1ull << (r & 63);
         if (mk[r >> 6] & bit) {
-            unmark(i);
+            unmark_edit(ctx, pe, i);
             return fail(ctx, FT_ERR_INVALID_ARGUMENT, "map update: index %d listed twice", r);
         }
         mk[r >> 6] |= bit;
     }
     const int n1 = n - nr;
     if ((int64_t)n1 + m > capacity) {
-        unmark(nr);
+        unmark_edit(ctx, pe, nr);
         return fail(ctx, FT_ERR_CAPACITY, "map update: %d points exceed the capacity %d", n1 + m, capacity);
-    }
-    // (hole, source) pairs: removed slots below n1 and surviving points from n1 up, both ascending
-    std::vector<int32_t> &holes = ctx->edit_holes;
-    holes.clear();
-    for (int w = 0; w < (n1 + 63) / 64; ++w) {
-        uint64_t bits = mk[w];
-        if (w == n1 / 64) bits &= (n1 % 64) ? ((1ull << (n1 % 64)) - 1) : 0ull;
-        while (bits) {
-            holes.push_back(w * 64 + __builtin_ctzll(bits));
-            bits &= bits - 1;
-        }
-    }
-    const int n_holes = (int)holes.size();
-    pe.pairs.resize(2 * (size_t)n_holes);
-    int src = n1;
-    for (int h = 0; h < n_holes; ++h) {
-        while (mk[src >> 6] & (1ull << (src & 63))) ++src;
-        pe.pairs[2 * h] = holes[h];
-        pe.pairs[2 * h + 1] = src++;
-    }
-    unmark(nr);
-    if (rec) {   // the moved points' record entries must be consistent before anything is enqueued
-        for (int h = 0; h < n_holes; ++h) {
-            const int id = rec->slot_id[pe.pairs[2 * h + 1]];
-            if (id < 0 || id >= rec->id_count || rec->slot_of[id] != pe.pairs[2 * h + 1])
-                return fail(ctx, FT_ERR_INVALID_ARGUMENT, "map update: id record inconsistent at slot %d",
-                            pe.pairs[2 * h + 1]);
-        }
     }
     pe.n1 = n1;
     pe.m = m;
-    pe.n_holes = n_holes;
+    pe.n_holes = nr;   // less the removed slots at or above n1
+    for (int w = n1 >> 6; w < (n + 63) / 64; ++w)
+        pe.n_holes -= __builtin_popcountll(w == n1 >> 6 ? mk[w] >> (n1 & 63) : mk[w]);
+    return FT_OK;
+}
+
+// The moves of a prepared edit, in order: the surviving points of the slots from
+// n1 up (ascending, 64 slots a word) take the removed slots below n1 (ascending;
+// as many as there are such points).  word(first slot) before each word's moves.
+template <class Word, class Move>
+void for_each_move(const ft_context *ctx, int n, const PreparedEdit &pe, Word word, Move move)
+{
+    const uint64_t *mk = ctx->edit_marks.data(), *hw = mk;
+    uint64_t holes = pe.n_holes > 0 ? *hw : 0;
+    for (int s0 = pe.n1 & ~63; s0 < n; s0 += 64) {
+        uint64_t src = ~mk[s0 >> 6];
+        if (s0 < pe.n1) src &= ~0ull << (pe.n1 & 63);
+        if (n - s0 < 64) src &= ~(~0ull << (n - s0));
+        word(s0);
+        for (; src; src &= src - 1, holes &= holes - 1) {
+            while (!holes) holes = *++hw;
+            move((int)(hw - mk) * 64 + __builtin_ctzll(holes), s0 + __builtin_ctzll(src));
+        }
+    }
+}
+
+// The moved point's entry in the edit's id record must be consistent.
+ft_status check_moved_id(ft_context *ctx, const ft_map_ids *rec, int src)
+{
+    const int id = rec->slot_id[src];
+    if (id < 0 || id >= rec->id_count || rec->slot_of[id] != src)
+        return fail(ctx, FT_ERR_INVALID_ARGUMENT, "map update: id record inconsistent at slot %d", src);
     return FT_OK;
 }
 
@@ -1550,18 +1563,19 @@ bool map_overlaps(const ft_map_points &map, int32_t capacity, const ft_map_point
 }
 
 // The id record follows an enqueued edit (removed ids leave, moved ids take
-// their holes, inserted ids follow n1).
-void commit_record(const ft_map_edit *edit, const PreparedEdit &pe)
+// their holes, inserted ids follow n1).  moves(f) calls f(hole, source) in order.
+template <class Moves>
+void commit_record(const ft_map_edit *edit, const PreparedEdit &pe, Moves moves)
 {
     ft_map_ids *rec = edit->ids;
     if (!rec) return;
     int32_t *sid = rec->slot_id, *sof = rec->slot_of;
     for (int32_t r : pe.rem) sof[sid[r]] = -1;
-    for (int h = 0; h < pe.n_holes; ++h) {
-        const int id = sid[pe.pairs[2 * h + 1]];
-        sid[pe.pairs[2 * h]] = id;
-        sof[id] = pe.pairs[2 * h];
-    }
+    moves([&](int hole, int src) {
+        const int id = sid[src];
+        sid[hole] = id;
+        sof[id] = hole;
+    });
     for (int j = 0; j < pe.m; ++j) {
         sid[pe.n1 + j] = edit->insert_ids[j];
         sof[edit->insert_ids[j]] = pe.n1 + j;
@@ -1604,6 +1618,8 @@ ft_status finish_edit_chunk(ft_context *ctx, size_t off, size_t need, hipStream_
 
 }  // namespace
 
+extern "C" {
+
 ft_status ft_map_update(ft_context *ctx, void *stream, ft_map_points *map, int32_t capacity,
                         const ft_map_edit *edit)
 {
@@ -1612,13 +1628,23 @@ ft_status ft_map_update(ft_context *ctx, void *stream, ft_map_points *map, int32
     PreparedEdit &pe = ctx->edit_one;
     if ((st = prepare_edit(ctx, map, capacity, edit, pe))) return st;
     // slots above the new count of survivors (the kernel reads none when no hole takes one)
-    const int tail = pe.n_holes > 0 ? map->n - pe.n1 : 0;
+    const int n = map->n, tail = pe.n_holes > 0 ? n - pe.n1 : 0;
     const size_t need = align_up(sizeof(int32_t) * (size_t)std::max(tail, 1), 256);
     size_t off = 0;
-    if ((st = take_edit_chunk(ctx, need, &off))) return st;
+    if ((st = take_edit_chunk(ctx, need, &off))) {
+        unmark_edit(ctx, pe, (int)pe.rem.size());
+        return st;
+    }
     int32_t *holes = reinterpret_cast<int32_t *>(ctx->edit_ring + off);
-    std::fill(holes, holes + tail, -1);
-    for (int h = 0; h < pe.n_holes; ++h) holes[pe.pairs[2 * h + 1] - pe.n1] = pe.pairs[2 * h];
+    if (tail > 0)
+        for_each_move(
+            ctx, n, pe,
+            [&](int s0) { std::fill(holes + std::max(s0 - pe.n1, 0), holes + std::min(s0 + 64 - pe.n1, tail), -1); },
+            [&](int hole, int src) { holes[src - pe.n1] = hole; });
+    unmark_edit(ctx, pe, (int)pe.rem.size());
+    if (edit->ids)
+        for (int i = 0; i < tail; ++i)
+            if (holes[i] >= 0 && (st = check_moved_id(ctx, edit->ids, pe.n1 + i))) return st;
     hipStream_t s = (hipStream_t)stream;
     MapEditArgs a{};
     a.pos = const_cast<float *>(map->pos);
@@ -1645,7 +1671,10 @@ ft_status ft_map_update(ft_context *ctx, void *stream, ft_map_points *map, int32
     }
     HIP_TRY(ctx, launch_map_edit(a, s));
     if ((st = finish_edit_chunk(ctx, off, need, s))) return st;
-    commit_record(edit, pe);
+    commit_record(edit, pe, [&](auto f) {
+        for (int i = 0; i < tail; ++i)
+            if (holes[i] >= 0) f(holes[i], pe.n1 + i);
+    });
     map->n = pe.n1 + pe.m;
     return FT_OK;
 }
@@ -1663,6 +1692,16 @@ ft_status ft_map_update_many(ft_context *ctx, void *stream, int32_t n, ft_map_po
     int64_t moves = 0, apps = 0;
     for (int i = 0; i < n; ++i) {
         if ((st = prepare_edit(ctx, maps[i], capacities[i], &edits[i], pe[i]))) return st;
+        pe[i].pairs.reserve(2 * (size_t)pe[i].n_holes);
+        if (pe[i].n_holes > 0)
+            for_each_move(ctx, maps[i]->n, pe[i], [](int) {}, [&](int hole, int src) {
+                pe[i].pairs.push_back(hole);
+                pe[i].pairs.push_back(src);
+            });
+        unmark_edit(ctx, pe[i], (int)pe[i].rem.size());
+        if (edits[i].ids)
+            for (int k = 0; k < pe[i].n_holes; ++k)
+                if ((st = check_moved_id(ctx, edits[i].ids, pe[i].pairs[2 * k + 1]))) return st;
         for (int k = 0; k < i; ++k) {
             if (maps[k]->pos == maps[i]->pos)
                 return fail(ctx, FT_ERR_INVALID_ARGUMENT, "map update many: edits %d and %d name one map", k, i);
@@ -1723,7 +1762,9 @@ ft_status ft_map_update_many(ft_context *ctx, void *stream, int32_t n, ft_map_po
                                       reinterpret_cast<const int32_t *>(d + d_bytes + m_bytes), (int)apps, s));
     if ((st = finish_edit_chunk(ctx, off, need, s))) return st;
     for (int i = 0; i < n; ++i) {
-        commit_record(&edits[i], pe[i]);
+        commit_record(&edits[i], pe[i], [&](auto f) {
+            for (int k = 0; k < pe[i].n_holes; ++k) f(pe[i].pairs[2 * k], pe[i].pairs[2 * k + 1]);
+        });
         maps[i]->n = pe[i].n1 + pe[i].m;
     }
     return FT_OK;
