@@ -668,13 +668,23 @@ ft_status enter(ft_context *ctx)
 // sorts: 176 us per batch with one, 179 with two, 185 with four).
 int setup_split(int sorts) { return 4 * sorts <= 256 ? 4 : 2 * sorts <= 256 ? 2 : 1; }
 
+// Map points and keypoints per thread of a single call's search resolve.  One frame
+// wants more and shorter waves than a batch, whose loads wait behind no branch for
+// a group past the end, until the counter's updates, one per wave, outweigh that (a
+// search call with 300 keypoints and 1,000 points: 15.3 us with one, 15.9 with
+// four; 3,000 and 20,000: 24.4 and 24.7; 8,000 and 60,000: 34.9 and 34.8; 12,000
+// and 60,000: 45.5 and 44.8).
+int final_per_one(const DevJob &J) { return std::max(J.L.n, J.R.n) > 8192 ? 4 : 1; }
+
 ft_status launch_one(ft_context *ctx, DevJob &J, hipStream_t s, bool stereo, bool search)
 {
     J.setup_split = setup_split((stereo ? 1 : 0) + (search ? J.n_views : 0));
+    Shapes sh = ctx->shapes;
+    sh.final_per = final_per_one(J);
     int32_t tot[PH_COUNT];
-    job_tiles(J, ctx->shapes, stereo, search, tot);
+    job_tiles(J, sh, stereo, search, tot);
     TileMap none{0, nullptr};
-    HIP_TRY(ctx, launch_pipeline(nullptr, none, tot, J, ctx->shapes, s, next_events(ctx, tot)));
+    HIP_TRY(ctx, launch_pipeline(nullptr, none, tot, J, sh, s, next_events(ctx, tot)));
     return FT_OK;
 }
 

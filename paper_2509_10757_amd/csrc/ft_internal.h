@@ -113,7 +113,7 @@ struct DevJob {
     int32_t flags;
     int32_t nM;
     int32_t n_views;
-    int32_t setup_split;             // workgroups of a row or cell sort (1, 2, 4 or 8)
+    int32_t setup_split;             // workgroups of a row or cell sort (1, 2 or 4)
     DevKps L, R;
     float sf[kLevels], inv_sf[kLevels], sigma2[kLevels];
     // pinhole stereo
@@ -167,6 +167,11 @@ struct Shapes {
     int best_lanes = 8;        // lanes cooperating on one pinhole left keypoint
     int search_lanes = 1;      // lanes cooperating on one map point (1 = record-dealt search)
     int aux_block = kAuxWG;    // threads per workgroup of the setup sorts and the stereo resolve
+    // map points and keypoints per thread of the search resolve (1 or 4; no choice of
+    // the caller's: a batch has waves enough, and four at once take a quarter of the
+    // loads and of the counter's updates: 64 mixed frames 156.9 us per batch with one,
+    // 151.2 with four)
+    int final_per = 4;
     bool operator==(const Shapes &o) const
     {
         return best_lanes == o.best_lanes && search_lanes == o.search_lanes && aux_block == o.aux_block;

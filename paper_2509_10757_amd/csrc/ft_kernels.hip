@@ -2259,36 +2259,38 @@ __device__ __forceinline__ void ph_search(const DevJob &J, const DevView &V, int
     finish_query<G>(J, V, m, sub, top);
 }
 
-constexpr int kFinalPer = 4;   // map points and keypoints per thread of the search resolve
-
-// Duplicate resolution and outputs: kFinalPer consecutive map points and
+// Duplicate resolution and outputs: kPer (1 or 4) consecutive map points and
 // keypoints per thread, their loads together.
+template <int kPer>
 __device__ __forceinline__ void ph_search_final(const DevJob &J, const DevView &V, int nK, int tile)
 {
-    const int i0 = (tile * kWG + (int)threadIdx.x) * kFinalPer;
-    auto load = [](const FT_G int32_t *p, int i, int n, int r[kFinalPer]) {
-        if (i + kFinalPer <= n) {
+    static_assert(kPer == 1 || kPer == 4, "a dword or four");
+    const int i0 = (tile * kWG + (int)threadIdx.x) * kPer;
+    auto load = [](const FT_G int32_t *p, int i, int n, int r[kPer]) {
+        if (kPer == 4 && i + kPer <= n) {
             const v4u v = *reinterpret_cast<const FT_G v4u_dw *>(p + i);
-            _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e) r[e] = (int)v[e];
+            _Pragma("unroll") for (int e = 0; e < kPer; ++e) r[e] = (int)v[e];
         } else {
-            _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e) r[e] = i + e < n ? p[i + e] : -1;
+            _Pragma("unroll") for (int e = 0; e < kPer; ++e) r[e] = i + e < n ? p[i + e] : -1;
         }
     };
-    auto store = [](FT_G int32_t *p, int i, int n, const int r[kFinalPer]) {
-        if (i + kFinalPer <= n) {
-            *reinterpret_cast<FT_G v4u_dw *>(p + i) = v4u{(uint32_t)r[0], (uint32_t)r[1], (uint32_t)r[2], (uint32_t)r[3]};
+    auto store = [](FT_G int32_t *p, int i, int n, const int r[kPer]) {
+        if (kPer == 4 && i + kPer <= n) {
+            v4u v;
+            _Pragma("unroll") for (int e = 0; e < 4; ++e) v[e] = (uint32_t)r[e % kPer];
+            *reinterpret_cast<FT_G v4u_dw *>(p + i) = v;
         } else {
-            _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e) if (i + e < n) p[i + e] = r[e];
+            _Pragma("unroll") for (int e = 0; e < kPer; ++e) if (i + e < n) p[i + e] = r[e];
         }
     };
-    int k[kFinalPer], h[kFinalPer], c[kFinalPer];
+    int k[kPer], h[kPer], c[kPer];
     load(V.mp_k, i0, J.nM, k);
     load(V.mp_h, i0, J.nM, h);
     load(reinterpret_cast<const FT_G int32_t *>(V.claim), i0, nK, c);
     if (i0 < J.nM) {
-        uint32_t cl[kFinalPer];
-        _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e) cl[e] = k[e] >= 0 ? V.claim[k[e]] : 0u;
-        _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e)
+        uint32_t cl[kPer];
+        _Pragma("unroll") for (int e = 0; e < kPer; ++e) cl[e] = k[e] >= 0 ? V.claim[k[e]] : 0u;
+        _Pragma("unroll") for (int e = 0; e < kPer; ++e)
         {
             const bool keep = k[e] >= 0 && cl[e] == (((uint32_t)h[e] << 23) | (uint32_t)(i0 + e));
             k[e] = keep ? k[e] : -1;
@@ -2298,7 +2300,7 @@ __device__ __forceinline__ void ph_search_final(const DevJob &J, const DevView &
         store(V.mp_dist, i0, J.nM, h);
     }
     int n = 0;   // (an unclaimed keypoint's claim is ~0, as is what lies past the last)
-    _Pragma("unroll") for (int e = 0; e < kFinalPer; ++e)
+    _Pragma("unroll") for (int e = 0; e < kPer; ++e)
     {
         const bool has = c[e] != -1;
         n += has ? 1 : 0;
@@ -2473,10 +2475,10 @@ __host__ __device__ inline int search_tiles_per_view(const DevJob &J, int lanes)
 }
 
 
-__host__ __device__ inline int final_tiles_view(const DevJob &J, int v)
+__host__ __device__ inline int final_tiles_view(const DevJob &J, int v, int per)
 {
     const int nK = view_kp(J, v);
-    return div_up(J.nM > nK ? J.nM : nK, kWG * kFinalPer);
+    return div_up(J.nM > nK ? J.nM : nK, kWG * per);
 }
 
 // Workgroups of the setup phase: J.setup_split for the row sort by level and
@@ -2509,7 +2511,7 @@ void job_tiles(const DevJob &J, const Shapes &s, bool do_stereo, bool do_search,
     }
     for (int v = 0; v < nv; ++v) {
         out[PH_SEARCH] += search_tiles_per_view(J, s.search_lanes);
-        out[PH_SEARCH_FIN] += final_tiles_view(J, v);
+        out[PH_SEARCH_FIN] += final_tiles_view(J, v, s.final_per);
     }
 }
 
@@ -2618,12 +2620,13 @@ __device__ __forceinline__ void task_search(const DevJob &J, int tile, unsigned 
     else ph_search<G>(J, J.view[v], tile - v * tpv);
 }
 
+template <int kPer>
 __device__ __forceinline__ void task_search_final(const DevJob &J, int tile)
 {
-    const int t0 = final_tiles_view(J, 0);
+    const int t0 = final_tiles_view(J, 0, kPer);
     const int v = tile < t0 ? 0 : 1;
     if (v >= J.n_views) return;
-    ph_search_final(J, J.view[v], view_kp(J, v), tile - (v ? t0 : 0));
+    ph_search_final<kPer>(J, J.view[v], view_kp(J, v), tile - (v ? t0 : 0));
 }
 
 static_assert(4 * kKnnQueriesPerWG * 2 * 4 <= kTaskLds, "stereo_a LDS");
@@ -2711,12 +2714,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7, 8))) void
     task_search<1>(src(job), tile, smem);
 }
 
-template <class Src>
+// (kPer: the launch's final_per)
+template <class Src, int kPer>
 __global__ __launch_bounds__(kWG) void k_search_final(Src src)
 {
     int job, tile;
     if (!src.locate(PH_SEARCH_FIN, job, tile)) return;
-    task_search_final(src(job), tile);
+    task_search_final<kPer>(src(job), tile);
 }
 
 // Last-frame search (one view of one job): search, then claims, rotation check
@@ -2878,7 +2882,10 @@ static void *phase_kernel(const Shapes &sh, int p, int *block)
         case 16: return reinterpret_cast<void *>(&k_search<Src, 16>);
         default: return reinterpret_cast<void *>(&k_search<Src, 4>);
         }
-    default: return reinterpret_cast<void *>(&k_search_final<Src>);
+    default:
+        if constexpr (std::is_same_v<Src, OneJob>)
+            if (sh.final_per == 1) return reinterpret_cast<void *>(&k_search_final<Src, 1>);
+        return reinterpret_cast<void *>(&k_search_final<Src, 4>);
     }
 }
 
