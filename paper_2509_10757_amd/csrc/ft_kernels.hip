@@ -2774,12 +2774,12 @@ hipError_t launch_last_frame(const DevJob &J, hipStream_t s)
     hipError_t e = launch(&k_setup<OneJob, kAuxWG>, setup_parts_view(J, 0), kAuxWG);
     if (e != hipSuccess) return e;
     if (J.nM > 0 && (e = launch(&k_last_search<OneJob>, div_up(J.nM, 64), 64)) != hipSuccess) return e;
-    // One workgroup holds kSortUnroll points per thread; a last frame has at most
-    // its keypoints' number of points, far fewer (1153 points and 1200 keypoints:
-    // 4 us against 14 us for the two kernels, whose launches and histogram
-    // updates it saves; keypoints are strided, so their number is bounded where
-    // more workgroups would be faster).
-    if (J.nM <= kSortUnroll * kAuxWG && nK <= 4 * kSortUnroll * kAuxWG) return launch(&k_last_finish<OneJob>, 1, kAuxWG);
+    // One workgroup holds kSortUnroll points per thread and strides the keypoints, which
+    // saves a launch and the histogram's updates in memory; with many keypoints more
+    // workgroups win (one kernel and two, per call: 1,200 keypoints and 1,153 points
+    // 18.1 and 20.8 us, 3,600 and 4,096 25.5 and 26.8, 8,000 and 1,153 38.3 and 38.9,
+    // 8,000 and 4,096 40.0 and 39.2, 16,000 and 4,096 65.4 and 62.2).
+    if (J.nM <= kSortUnroll * kAuxWG && nK <= 2 * kSortUnroll * kAuxWG) return launch(&k_last_finish<OneJob>, 1, kAuxWG);
     if (J.nM > 0 && (e = launch(&k_last_resolve<OneJob>, div_up(J.nM, kWG), kWG)) != hipSuccess) return e;
     return launch(&k_last_final<OneJob>, div_up(J.nM > nK ? J.nM : nK, kWG), kWG);
 }
