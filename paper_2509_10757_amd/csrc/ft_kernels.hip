@@ -277,9 +277,10 @@ void pyr_plan(DevJob &J, int rows_log2)
 // hold all four pixel pairs while s <= 11/3; realigned to the first tap, column
 // k's pair starts floor(k s) or one more bytes in, so it lies in a fixed pair of
 // dwords: the first two for every column while s <= 2 (kNear), later ones for
-// columns 2 and 3 beyond (kMid, kFar).  kAny, for any other level or an image
-// under 16 columns, reads the pixels one by one.
-enum PyrReach { kNear, kMid, kFar, kAny };
+// columns 2 and 3 beyond (kMid, kFar); past 11/3 each column reads the dword pair
+// that holds its own (kPairs).  kAny, for an image under 16 columns or a strip that
+// reaches the image's last bytes, reads the pixels one by one.
+enum PyrReach { kNear, kMid, kFar, kPairs, kAny };
 
 // Columns x .. x + 3 of output rows [ylo, yhi) of one level; `row_taps`: lane r
 // holds the row tap of output row ylo + r.  A lane reads one aligned dwordx4
@@ -310,13 +311,22 @@ __device__ __forceinline__ void pyr_resample(const FT_G uint8_t *src, int W, int
         sel[k] = 0x0C010C00u + 0x00010001u * (uint32_t)(x0[k] - x0[0] - first);
     }
     struct Row {
-        uint32_t d[4];
+        uint32_t d[kReach == kPairs ? 2 * kPyrCols : 4];
     };
     auto load = [&](const FT_G uint8_t *row) {
         Row v;
         if constexpr (kReach == kAny) {   // (a pixel pair per column, in place)
             _Pragma("unroll") for (int k = 0; k < kPyrCols; ++k)
                 v.d[k] = (uint32_t)row[x0[k]] | ((uint32_t)row[min(x0[k] + 1, W - 1)] << 16);
+        } else if constexpr (kReach == kPairs) {
+            typedef uint32_t v2u_dw __attribute__((ext_vector_type(2), aligned(4)));
+            const uint32_t sh = (uint32_t)reinterpret_cast<uintptr_t>(row) & 3u;
+            _Pragma("unroll") for (int k = 0; k < kPyrCols; ++k)
+            {
+                const v2u_dw q = *reinterpret_cast<const FT_G v2u_dw *>(row - sh + (((uint32_t)x0[k] + sh) & ~3u));
+                v.d[2 * k] = q[0];
+                v.d[2 * k + 1] = q[1];
+            }
         } else {
             // (past the row's end lie the next row's bytes, whose weights are 0)
             const uint32_t sh = (uint32_t)reinterpret_cast<uintptr_t>(row) & 3u;
@@ -328,7 +338,7 @@ __device__ __forceinline__ void pyr_resample(const FT_G uint8_t *src, int W, int
     };
     auto blend = [&](const Row &v, uint32_t sh, uint32_t h[kPyrCols]) {
         uint32_t e[4] = {v.d[0], v.d[1], v.d[2], v.d[3]};
-        if constexpr (kReach != kAny) {
+        if constexpr (kReach < kPairs) {
             const uint32_t a = (uint32_t)x0[0] + sh;   // (v_alignbyte takes it modulo 4)
             _Pragma("unroll") for (int i = 0; i < 3; ++i) e[i] = __builtin_amdgcn_alignbyte(v.d[i + 1], v.d[i], a);
             e[3] = __builtin_amdgcn_alignbyte(0u, v.d[3], a);
@@ -336,7 +346,11 @@ __device__ __forceinline__ void pyr_resample(const FT_G uint8_t *src, int W, int
         _Pragma("unroll") for (int k = 0; k < kPyrCols; ++k)
         {
             const int j = kReach == kFar && k == 3 ? 2 : kReach >= kMid && k >= 2 ? 1 : 0;
-            const uint32_t pr = kReach == kAny ? e[k] : __builtin_amdgcn_perm(e[j + 1], e[j], sel[k]);
+            uint32_t pr;
+            if constexpr (kReach == kAny) pr = e[k];
+            else if constexpr (kReach == kPairs)   // bytes o and o + 1 of the pair, o the first one's place in its dword
+                pr = __builtin_amdgcn_perm(v.d[2 * k + 1], v.d[2 * k], 0x0C010C00u + 0x00010001u * (((uint32_t)x0[k] + sh) & 3u));
+            else pr = __builtin_amdgcn_perm(e[j + 1], e[j], sel[k]);
             h[k] = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, pr), __builtin_bit_cast(u16x2, wgt[k]), 0u, false);
         }
     };
@@ -518,15 +532,18 @@ __device__ __forceinline__ void ph_pyramid(const DevJob &J, int tile)
     FT_G uint8_t *out = dst + off;
     // (column 3's pair ends ceil(3 s) + 1 bytes after the first tap, which is up
     // to 3 past its dword: 16 bytes while 3 s <= 11; columns 2 and 3 start at
-    // least 4 bytes in from s = 2, column 3 at least 9 from s = 10/3)
+    // least 4 bytes in from s = 2, column 3 at least 9 from s = 10/3).  Beyond, two
+    // dwords a column: with a scale factor of 2 a 1536x4096 image takes 8.6 us, read
+    // pixel by pixel 17.5, and 1536x1080 6.3 and 11.4.
     const bool full = kPyrStripW * (bx + 1) <= wl;
     // a strip that reads the image's last row (its own last row's taps, or the one
     // before where the level is as tall as the image) and, with 16 bytes per
     // lane, past that row's end (the last lane within 24 columns of it)
     const bool corner = yhi >= hl - 1 && kPyrStripW * (bx + 1) + 20 >= wl;
-    if (corner || W < 16 || 3 * W > 11 * wl) pyr_resample<kAny>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
+    if (corner || W < 16) pyr_resample<kAny>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
     else if (W <= 2 * wl) pyr_resample<kNear>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
     else if (3 * W <= 10 * wl) pyr_resample<kMid>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
+    else if (3 * W > 11 * wl) pyr_resample<kPairs>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
     else pyr_resample<kFar>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
 }
 
