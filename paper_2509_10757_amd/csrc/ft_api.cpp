@@ -415,7 +415,7 @@ ft_status build_pinhole(ft_context *ctx, DevJob &J, const ft_keypoints *L, const
     J.th_orb = p->th_orb;
     J.half_win = p->half_win;
     J.half_range = p->half_range;
-    J.level_window = p->level_window;
+    J.level_window = std::min(p->level_window, kMaxWindow);
     J.med_num = p->median_num;
     J.med_den = p->median_den;
     J.o_right_idx = o->right_idx;

@@ -17,7 +17,7 @@ constexpr int kMaxCells = 8192;
 constexpr int kMaxKp = 65535;
 constexpr int kMaxCellRep = 3;       // copies of a keypoint in a level-binned cell index (level window <= 3 octaves)
 constexpr int kMaxMap = (1 << 23) - 1;
-constexpr int kMaxWindow = 255;      // octaves a search window reaches each way (octaves are bytes: more is the same)
+constexpr int kMaxWindow = 255;      // octaves a level window reaches each way (octaves are bytes: more is the same)
 constexpr int kKnnQueriesPerWG = 32;  // fisheye all-pairs: queries per 256-thread subgroup (16-row MFMA blocks)
 constexpr int kKnnTilesInFlight = 4;  // fisheye all-pairs: target tiles whose descriptor loads a wave keeps in flight
 constexpr int kRefinePerWG = 4;       // pinhole refinement: one wave per match

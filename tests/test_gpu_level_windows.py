@@ -45,3 +45,23 @@ def test_wide_windows_equal_oracle(ft, ctx, lo, hi, lanes):
         compare_frame(df.results(), want)
     levels = np.unique(f["left"]["octave"][want["search"][0]["mp_match"][want["search"][0]["mp_match"] >= 0]])
     assert len(levels) > 3
+
+
+@pytest.mark.parametrize("rows", [160, 1100])
+@pytest.mark.parametrize("window", [7, 255, 256, 65536, INT_MAX - 3, INT_MAX])
+def test_wide_stereo_windows_equal_oracle(ft, window, rows):
+    """The stereo level window: row bins per level (8 x 160) and one for every level."""
+    ctx = ft.Context(ft.default_limits(max_kp_per_image=512, max_map_points=512, max_rows=2048, max_batch_frames=1,
+                                       max_inflight=1))
+    f = synth.tiny_pinhole(55, n_kp=400)
+    f["stereo_cam"] = dict(f["stereo_cam"], rows=rows)
+    want = oracle.run_frame(dict(f, stereo_params=dict(f["stereo_params"], level_window=7)))
+    assert want["stereo"]["n_matches"] > 50
+    for batch in (False, True):
+        df = ft.DeviceFrame(dict(f, stereo_params=dict(f["stereo_params"], level_window=window)), "cuda")
+        if batch:
+            ctx.ft_batch_wait(ctx.ft_batch_submit([df.job()]))
+        else:
+            df.run(ctx)
+        torch.cuda.synchronize()
+        compare_frame(df.results(), want)
