@@ -65,9 +65,6 @@ typedef v4u v4u_dw __attribute__((aligned(4)));
 // the median pass (a strided loop body unrolled; surplus entries masked).
 constexpr int kSortUnroll = 4;
 
-// Candidates of a scan whose descriptors are read in one round.
-constexpr int kCandBatch = 3;
-
 // Candidates whose loads are issued together in the best-match and search scans.
 constexpr int kBestUnroll = 2;
 constexpr int kSearchUnroll = 2;
@@ -1011,63 +1008,6 @@ __device__ __forceinline__ void ph_best(const DevJob &J, int tile)
         J.best_h[i] = ok ? h : -1;
     }
     append_match(J, sub == 0 && i < J.L.n && ok, match_rec(i, best, bx, x, y, oi));
-}
-
-// Row-band scan of one pinhole left keypoint over staged (LDS) or global row
-// records: lane `sub` of G takes every G-th record of the bins row +- reach;
-// the candidates are collected first (kCandBatch at a time) and their
-// row-ordered descriptors then read together (as in the wide search).
-template <int G>
-__device__ __forceinline__ void best_scan(const DevJob &J, const int *rs, const RowRec *rr, int row, int oi,
-                                          float minU, float maxU, const Desc &di, int sub, uint32_t &best,
-                                          float &bx)
-{
-    int lb0, lb1;
-    level_bins(J, oi, lb0, lb1);
-    int done = 0;
-    for (;;) {
-        int n = 0, seen = 0;
-        int cp[kCandBatch];
-        _Pragma("unroll") for (int e = 0; e < kCandBatch; ++e) cp[e] = 0;
-        for (int lb = lb0; lb <= lb1; ++lb) {
-        const int reach = pick_level(J.lv_reach, lb);
-        const int *rsl = rs + lb * (J.rows + 1);
-        const int b0 = max(row - reach, 0);
-        const int b1 = min(row + reach, J.rows - 1);
-        const int p1 = rsl[b1 + 1];
-        for (int p = rsl[b0] + sub; p < p1; p += G) {
-            const RowRec rec = rr[p];
-            const int lo = (int)(rec.band & 0xFFFFu), hi = (int)(rec.band >> 16);
-            const int oj = (int)(rec.meta & 0xFFu);
-            if (row < lo || row > hi || oj < oi - J.level_window || oj > oi + J.level_window ||
-                !(rec.x >= minU && rec.x <= maxU))
-                continue;
-            if (seen >= done && n < kCandBatch) {
-                _Pragma("unroll") for (int e = 0; e < kCandBatch; ++e) if (n == e) cp[e] = p;
-                ++n;
-            }
-            ++seen;
-        }
-        }
-        Desc d[kCandBatch];
-        _Pragma("unroll") for (int e = 0; e < kCandBatch; ++e)
-        {
-            if (e < n) d[e] = load_desc(J.R.desc, (int)(rr[cp[e]].meta >> 16));
-        }
-        _Pragma("unroll") for (int e = 0; e < kCandBatch; ++e)
-        {
-            if (e < n) {
-                const RowRec rec = rr[cp[e]];
-                const uint32_t key = ((uint32_t)hamming(di, d[e]) << 16) | (rec.meta >> 16);
-                if (key < best) {
-                    best = key;
-                    bx = rec.x;
-                }
-            }
-        }
-        done += n;
-        if (done >= seen) break;
-    }
 }
 
 // ----------------------------- stereo_a (fisheye): all-pairs top-2 on MFMA
