@@ -350,7 +350,11 @@ void bind_pyramid_build(DevJob &J, const ft_image *L, const ft_image *R, const f
     }
     // Rows of a wave's strip, by the images built in one launch: short strips
     // fill the chip with one image (1281x719: 7.2 us at 4 rows, 10.9 at 16), long
-    // ones spread a strip's set-up over more rows (32 images of 752x480 and more)
+    // ones spread a strip's set-up over more rows.  Batches of images at 4, 8 and 16
+    // rows, us: 8 of 1281x719 40.9, 38.3, 40.5; 16 of them 56.7, 50.3, 48.6; 32 of
+    // them 86.1, 72.6, 67.9; 20 of 752x480 43.1, 40.2, 39.4; 48 of them 64.7, 56.8,
+    // 54.7; up to 12 of 752x480 and 32 of 376x240 within 1 us of one another.  (An image
+    // a few pixels wide and thousands of rows tall has mostly idle lanes: 16x4096 7.2.)
     pyr_plan(J, images <= 2 ? 2 : images <= 16 ? 3 : 4);
 }
 
@@ -665,7 +669,10 @@ ft_status enter(ft_context *ctx)
 // view of 3000 keypoints, 20,000 map points: 26.3 us per search call with one
 // workgroup, 25.1 with two, 23.1 with four, 22.9 with eight); a batch that fills
 // them has one each, since every part reads all keypoints (64 mixed frames, 160
-// sorts: 176 us per batch with one, 179 with two, 185 with four).
+// sorts: 176 us per batch with one, 179 with two, 185 with four).  Batches of
+// frames of 600 and 1,200 keypoints with one, two and four, us: 44 sorts 59.4, 58.1,
+// 57.3; 66 sorts 63.2, 62.0, 61.0; 96 sorts 69.4, 68.4, 68.5; 120 sorts 74.4, 73.3,
+// 73.4; 160 sorts 84.3, 84.2, 86.5; 200 sorts 90.4, 90.2, 92.4.
 int setup_split(int sorts) { return 4 * sorts <= 256 ? 4 : 2 * sorts <= 256 ? 2 : 1; }
 
 // Map points and keypoints per thread of a single call's search resolve.  One frame

@@ -266,7 +266,7 @@ struct OrbDetectArgs {
     int32_t tile0[kLevels + 1];       // first tile of each level; tile0[kLevels] = tiles
     int32_t t, edge, capacity, lds_w; // lds_w: LDS row stride (the widest level, rounded up to 4)
     // single-pass emission: tiles are taken by ticket (ticket counter - ticket_base), and each
-    // publishes its count and then its inclusive prefix in tile_state, tagged with this call's epoch
+    // publishes its count in tile_state, tagged with this call's epoch, and sums those before it
     FT_G unsigned long long *tile_state;  // [kOrbMaxTiles]
     FT_G uint32_t *ticket;
     uint32_t ticket_base, epoch;

@@ -1,8 +1,10 @@
 // HIP kernels of the tracking correspondence search for gfx950 (MI355X).
 //
-// Every kernel runs 256-thread workgroups (four 64-wide waves) and is written
-// as phase functions over one frame job, so the single-frame calls and the
-// batched submissions execute the very same code.  Build flags:
+// Every kernel is written as phase functions over one frame job, so the
+// single-frame calls and the batched submissions execute the very same code.
+// Workgroups have 256 threads (four 64-wide waves), but for the set-up sorts and the
+// stereo resolve (1024, or 256 by the launch shapes), the one-workgroup last-frame
+// resolve (1024) and the record-dealt searches (one wave).  Build flags:
 // -ffp-contract=off (no fused multiply-add: every float expression rounds
 // exactly as written) with correctly rounded fp32 divide and sqrt.
 //
@@ -52,14 +54,15 @@ struct Desc {
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 // A dword at any byte address; four dwords from a dword boundary.
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef v4u v4u_dw __attribute__((aligned(4)));
+
 // Constant address space: memory that no kernel running with the reader writes.
 #if defined(__HIP_DEVICE_COMPILE__)
 #define FT_C __attribute__((address_space(4)))
 #else
 #define FT_C
 #endif
-typedef uint32_t u32_any __attribute__((aligned(1)));
-typedef v4u v4u_dw __attribute__((aligned(4)));
 
 // Keypoints per thread whose loads are issued together in the setup sorts and
 // the median pass (a strided loop body unrolled; surplus entries masked).
