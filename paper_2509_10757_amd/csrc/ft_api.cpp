@@ -111,9 +111,10 @@ struct ft_context {
     double phase_ms[kPhases] = {};
     int64_t phase_n[kPhases] = {};
     std::vector<std::pair<char *, size_t>> host_blocks;   // ft_host_alloc blocks (upload sources)
-    // map edits: (hole, source) pairs written to a pinned ring that the move
-    // kernel reads over the bus; an edit's chunk is reclaimed once the event
-    // recorded after its kernels has completed (oldest first)
+    // map edits: each tail slot's hole (or, for several maps, descriptors and move and
+    // append lists) written to a pinned ring, which the kernel of a single edit reads
+    // over the bus; an edit's chunk is reclaimed once the event recorded after its
+    // kernels has completed (oldest first)
     struct EditChunk {
         size_t off, bytes;
         hipEvent_t ev;

@@ -3,7 +3,7 @@ the strip heights that a launch picks by its number of images (4 rows up to 2
 images, 8 up to 16, 16 beyond), images of odd widths, padded rows and rows that
 begin at any byte; and levels smaller by any scale, at full strip width, so that
 every way of reading the four columns' taps runs: scales up to 2, up to 10/3, up
-to 11/3, and beyond, where pixels are read one by one."""
+to 11/3, and beyond, where each column has a dword pair of its own."""
 import numpy as np
 import pytest
 import torch
