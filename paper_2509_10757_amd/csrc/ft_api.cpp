@@ -354,8 +354,7 @@ void bind_pyramid_build(DevJob &J, const ft_image *L, const ft_image *R, const f
     // ones spread a strip's set-up over more rows.  Batches of images at 4, 8 and 16
     // rows, us: 8 of 1281x719 40.9, 38.3, 40.5; 16 of them 56.7, 50.3, 48.6; 32 of
     // them 86.1, 72.6, 67.9; 20 of 752x480 43.1, 40.2, 39.4; 48 of them 64.7, 56.8,
-    // 54.7; up to 12 of 752x480 and 32 of 376x240 within 1 us of one another.  (An image
-    // a few pixels wide and thousands of rows tall has mostly idle lanes: 16x4096 7.2.)
+    // 54.7; up to 12 of 752x480 and 32 of 376x240 within 1 us of one another.
     pyr_plan(J, images <= 2 ? 2 : images <= 16 ? 3 : 4);
 }
 

@@ -278,8 +278,8 @@ void pyr_plan(DevJob &J, int rows_log2)
 // k's pair starts floor(k s) or one more bytes in, so it lies in a fixed pair of
 // dwords: the first two for every column while s <= 2 (kNear), later ones for
 // columns 2 and 3 beyond (kMid, kFar); past 11/3 each column reads the dword pair
-// that holds its own (kPairs).  kAny, for an image under 16 columns or a strip that
-// reaches the image's last bytes, reads the pixels one by one.
+// that holds its own (kPairs).  kAny, for a strip that reaches the image's last
+// bytes, reads the pixels one by one.
 enum PyrReach { kNear, kMid, kFar, kPairs, kAny };
 
 // Columns x .. x + 3 of output rows [ylo, yhi) of one level; `row_taps`: lane r
@@ -435,6 +435,42 @@ __device__ __forceinline__ void pyr_resample(const FT_G uint8_t *src, int W, int
     }
 }
 
+// Rows [ylo, yhi) of a level at most 64 columns wide, a column per lane and byte
+// loads: with four columns per lane most lanes idle, and a tall image's strips are
+// bound by their number of instructions (16x4096: 7.2 us with four columns per lane,
+// 5.3 with one).  Level 0 too: its taps are the pixels themselves.
+__device__ __forceinline__ void pyr_narrow(const FT_G uint8_t *src, int W, int H, int pitch, FT_G uint8_t *dst, int wl,
+                                           int ylo, int yhi, uint32_t row_taps)
+{
+    const int lane = threadIdx.x & 63;
+    const uint32_t c = pyr_tap(min(lane, wl - 1), W, wl);
+    const uint32_t a = c >> 16;
+    const FT_G uint8_t *s0 = src + (c & 0xFFFFu), *s1 = src + min((int)(c & 0xFFFFu) + 1, W - 1);
+    FT_G uint8_t *d = dst + (size_t)ylo * wl + lane;
+    constexpr int kChunk = 4;   // output rows whose loads are issued together
+    for (int r0 = 0; r0 < yhi - ylo; r0 += kChunk) {
+        uint32_t p[kChunk][4], b[kChunk];
+        _Pragma("unroll") for (int u = 0; u < kChunk; ++u)
+        {
+            const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)row_taps, min(r0 + u, yhi - ylo - 1));
+            const int ys = (int)(t & 0xFFFFu);
+            const int64_t o0 = (int64_t)ys * pitch, o1 = (int64_t)min(ys + 1, H - 1) * pitch;
+            p[u][0] = s0[o0];
+            p[u][1] = s1[o0];
+            p[u][2] = s0[o1];
+            p[u][3] = s1[o1];
+            b[u] = t >> 16;
+        }
+        _Pragma("unroll") for (int u = 0; u < kChunk; ++u)
+        {
+            const uint32_t top = p[u][0] * (256u - a) + p[u][1] * a, bot = p[u][2] * (256u - a) + p[u][3] * a;
+            const uint32_t o = __umul24(bot, b[u]) + (__umul24(top, 256u - b[u]) + 32768u);
+            if (r0 + u < yhi - ylo && lane < wl) d[0] = (uint8_t)(o >> 16);
+            d += wl;
+        }
+    }
+}
+
 // Rows [ylo, yhi) of level 0: a lane takes dwords lane, lane + 64, .. of the
 // 1024-byte strip bx of each destination row, counted from the row's dword
 // boundary (neighbouring lanes on neighbouring dwords), realigned from the
@@ -521,7 +557,7 @@ __device__ __forceinline__ void ph_pyramid(const DevJob &J, int tile)
         ++bx;
     }
     const int ylo = by << rl, yhi = min(ylo + (1 << rl), hl);
-    if (l == 0) {
+    if (l == 0 && W > 64) {
         pyr_copy(src, W, pitch, dst, bx, ylo, yhi);
         return;
     }
@@ -540,7 +576,8 @@ __device__ __forceinline__ void ph_pyramid(const DevJob &J, int tile)
     // before where the level is as tall as the image) and, with 16 bytes per
     // lane, past that row's end (the last lane within 24 columns of it)
     const bool corner = yhi >= hl - 1 && kPyrStripW * (bx + 1) + 20 >= wl;
-    if (corner || W < 16) pyr_resample<kAny>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
+    if (wl <= 64) pyr_narrow(src, W, H, pitch, out, wl, ylo, yhi, taps);
+    else if (corner) pyr_resample<kAny>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
     else if (W <= 2 * wl) pyr_resample<kNear>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
     else if (3 * W <= 10 * wl) pyr_resample<kMid>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);
     else if (3 * W > 11 * wl) pyr_resample<kPairs>(src, W, H, pitch, out, wl, x, ylo, yhi, taps, full);

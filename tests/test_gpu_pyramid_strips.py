@@ -87,3 +87,20 @@ def test_scale_factors(ft, ctx, factor, W, H, pitch, shift):
     ctx.ft_build_pyramid(ft.ft_image(src.data_ptr() + shift, W, H, pitch), scales, lay)
     torch.cuda.synchronize()
     check(out.cpu().numpy(), img, sc["inv_sf"], (factor, W, H))
+
+
+@pytest.mark.parametrize("W", [64, 65, 66, 76, 77, 78, 92, 93])
+@pytest.mark.parametrize("H,pad,shift", [(9, 0, 0), (131, 3, 1), (1000, 0, 3)])
+def test_narrow_levels(ft, ctx, W, H, pad, shift):
+    """Images and levels of 64 columns (a column per lane) and of one more (four)."""
+    scales = ft._scales(SC)
+    lay, n = ft.pyramid_layout(W, H, scales)
+    img = np.random.default_rng(W * H).integers(0, 256, (H, W), dtype=np.uint8)
+    src = on_device(img, W + pad, shift)
+    out = torch.full((n + 1,), 0xA5, dtype=torch.uint8, device="cuda")
+    lay.data = out.data_ptr()
+    ctx.ft_build_pyramid(ft.ft_image(src.data_ptr() + shift, W, H, W + pad), scales, lay)
+    torch.cuda.synchronize()
+    host = out.cpu().numpy()
+    check(host[:n], img, SC["inv_sf"], (W, H))
+    assert host[n] == 0xA5
